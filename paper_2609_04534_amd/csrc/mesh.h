@@ -1,0 +1,141 @@
+// Parts shared by the kernels of a uniform box mesh: the mesh arguments, the
+// 1D tables of the coupled SIPG operator, tile orders and the PCG state.
+#pragma once
+
+#include "device.h"
+
+namespace tpfdm {
+
+// Device-side state of a PCG solve (pcg.hip; the multigrid kernels of a
+// solve read its done flag).  done: 0 running, 1 converged, 2 breakdown or
+// a non-finite scalar, 3 iteration limit.
+struct PcgState {
+    double rz, pq, rr, bb, alpha, beta, tol2;
+    int iter, done, maxit;
+    int norm;   // stopping test on 0: (r, r), 1: (r, z) (tol2 scaled to match)
+};
+
+// Sum of a double over the 64 lanes of a wave.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+struct MeshArgs {
+    int64_t ncells;
+    int64_t offset;
+    int logB;
+    int mx, my, mz;
+    double sx, sy, sz;   // s_d = h_o1 h_o2 / h_d
+};
+
+template <int N, typename T>
+struct FaceRef {        // reference endpoint derivatives and penalty C p (p+1)
+    T g0[N];
+    T g1[N];
+    T sigma;
+};
+
+// Tiles [first, first + count) of the XCD that runs workgroup b (b % 8), and
+// b's place in them: each XCD gets a contiguous range of the nwg tiles (the
+// first nwg % 8 ranges hold one tile more), so that neighbours of its tiles
+// share its L2 (100^3 cells at n = 4 in FP64, 7813 tiles: 315 us against 450
+// us in launch order).
+struct XcdRange {
+    unsigned first, count, place;
+};
+__device__ __forceinline__ XcdRange xcd_range(unsigned b, unsigned nwg) {
+    const unsigned q = nwg / 8, r = nwg % 8, x = b % 8;
+    return {x * q + (x < r ? x : r), q + (x < r ? 1u : 0u), b / 8};
+}
+// Tile of workgroup b in that order.
+__device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned nwg) {
+    const XcdRange x = xcd_range(b, nwg);
+    return x.first + x.place;
+}
+
+// Tile of workgroup b for the one-cell-per-lane kernels of a mesh plan (about
+// S tiles per x-plane of cells).  Each XCD walks its range in groups of
+// kLaneSweep consecutive tiles carried through the range's rows of S tiles:
+// a tile's x neighbours then come kLaneSweep tiles apart in the visiting
+// order instead of S, and are still in the XCD's L2 when the second of them
+// reads them.  A bijection on [0, nwg): the last group of a row is S mod
+// kLaneSweep wide when kLaneSweep does not divide S; the part of the range
+// past its last whole row, and S = 0, keep the plain order.
+constexpr unsigned kLaneSweep = 8;
+
+__device__ __forceinline__ unsigned lane_tile(unsigned b, unsigned nwg, unsigned S) {
+    const XcdRange x = xcd_range(b, nwg);
+    const unsigned l = x.place;
+    if (S == 0) return x.first + l;
+    const unsigned R = x.count / S;
+    if (R < 2 || l >= R * S) return x.first + l;
+    const unsigned full = (S / kLaneSweep) * kLaneSweep * R;   // tiles in whole-width groups
+    if (l < full) {
+        const unsigned chunk = l / (kLaneSweep * R), r = (l / kLaneSweep) % R, g = l % kLaneSweep;
+        return x.first + r * S + chunk * kLaneSweep + g;
+    }
+    const unsigned w = S % kLaneSweep, e = l - full;          // w > 0 here
+    return x.first + (e / w) * S + (S - w) + e % w;
+}
+
+// Row length S for lane_tile: the whole tiles of 64 W cells in an x-plane of
+// cells when one plane of blocks (n^3 values of T per cell) holds 2 MiB or
+// more, else 0 (plain order).  Coupled operator at n = 4, plain against
+// grouped order: FP64 128^3 cells (8 MiB planes) 663 / 568 us, 100^3 354 /
+// 315 us, 64^3 (2 MiB) 79 / 72 us; FP32 128^3 358 / 346 us; Hermite-type
+// basis 128^3 500 / 479 us.  Groups of 4 to 32 tiles differ by under 5%; at
+// n = 2 with 1 MiB planes the grouped order took 50 us against 46.
+template <int N, typename T, int W>
+__device__ __forceinline__ unsigned plane_tiles(const MeshArgs& G) {
+    constexpr int64_t kMinPlaneBytes = int64_t(2) << 20;
+    const int64_t p = static_cast<int64_t>(G.my) * G.mz;
+    if (p * N * N * N * static_cast<int64_t>(sizeof(T)) < kMinPlaneBytes) return 0u;
+    return static_cast<unsigned>(p / (64 * W));
+}
+
+// Kernel arguments of a mesh plan's group.
+inline MeshArgs mesh_args(const Plan& plan, const GroupInfo& g) {
+    MeshArgs G;
+    G.ncells = g.nblocks;
+    G.offset = g.offset;
+    G.logB = g.logB;
+    G.mx = plan.mesh_m[0];
+    G.my = plan.mesh_m[1];
+    G.mz = plan.mesh_m[2];
+    const double hx = plan.mesh_h[0], hy = plan.mesh_h[1], hz = plan.mesh_h[2];
+    G.sx = hy * hz / hx;
+    G.sy = hx * hz / hy;
+    G.sz = hx * hy / hz;
+    return G;
+}
+
+// 1D tables of the coupled operator: M_hat and the cell-diagonal P_hat
+// (A_hat, or A_hat - K_hat for the face part alone), endpoint derivatives and
+// the reference penalty.
+template <int N, typename TC>
+void sipg_tables(const Plan& plan, bool face_only, Pair<N, TC>& R, FaceRef<N, TC>& F) {
+    const RefData& ref = plan.ref[N];
+    for (int i = 0; i < N * N; ++i) {
+        R.m[i] = static_cast<TC>(ref.M[i]);
+        R.p[i] = static_cast<TC>(face_only ? ref.A[i] - ref.K[i] : ref.A[i]);
+    }
+    for (int i = 0; i < N; ++i) {
+        F.g0[i] = static_cast<TC>(ref.g0[i]);
+        F.g1[i] = static_cast<TC>(ref.g1[i]);
+    }
+    F.sigma = static_cast<TC>(plan.penalty_C * (N - 1) * N);
+}
+
+// The wave kernels of the Hermite-type basis work in the sign-flipped
+// coefficients (see wave_sipg_cell): endpoint derivatives D g.
+template <int N, typename T>
+void flip_face_ref(FaceRef<N, T>& F) {
+    for (int k = 0; k < N; ++k) {
+        F.g0[k] = static_cast<T>(hermite_sign(N, k)) * F.g0[k];
+        F.g1[k] = static_cast<T>(hermite_sign(N, k)) * F.g1[k];
+    }
+}
+
+}  // namespace tpfdm

@@ -60,85 +60,79 @@ __device__ __forceinline__ bool done_flag(const PcgState* st) { return st && st-
 template <typename TS>
 using MgTC = typename std::conditional<std::is_same<TS, float>::value, float, double>::type;
 
-// Minimum resident waves per SIMD the lane operator-row kernels are built
-// for: four for the FP32 rows of the Hermite-type basis (126 VGPRs, no
-// spills; 3% faster MG-PCG at p = 3 on 128^3 cells than at three waves),
-// otherwise two (the FP32 Lagrange rows spill 164 bytes per lane at four).
-template <typename TS, bool HERM, typename TI>
-constexpr int mg_lane_waves() {
-    return sizeof(TS) == 4 && sizeof(TI) == 4 && HERM ? 4 : 2;
-}
-
-// t = A u on one level (one cell per lane); the consumers form b - t as
-// they load, which keeps b out of this kernel's registers.
-template <int N, bool HERM, typename TS>
-__global__ __launch_bounds__(64, (mg_lane_waves<TS, HERM, TS>())) void k_mg_apply(const TS* __restrict__ u, TS* __restrict__ t, MeshArgs G,
-                                                  Pair<N, MgTC<TS>> R, FaceRef<N, MgTC<TS>> F,
-                                                  const PcgState* __restrict__ st) {
+// t = A u on one level (64 W cells per workgroup of N waves); the consumers
+// form b - t as they load.
+template <int N, bool HERM, typename TS, int W = 1>
+__global__ __launch_bounds__(64 * N, (tile_waves<N, MgTC<TS>, W>())) void k_mg_apply(
+    const TS* __restrict__ u, TS* __restrict__ t, MeshArgs G, TileTab<N, MgTC<TS>, HERM> R,
+    const PcgState* __restrict__ st) {
     using TC = MgTC<TS>;
     if (done_flag(st)) return;
-    constexpr int N3 = N * N * N;
-    __shared__ TC sa[N * N][64], sbt[N * N][64];
-    const int64_t c = static_cast<int64_t>(lane_tile(blockIdx.x, gridDim.x, plane_tiles<N, TS, HERM>(G))) * 64 + threadIdx.x;
-    if (c >= G.ncells) return;
-    TC acc[N3];
-    sipg_cell<N, TS, TC, -1, HERM>(u, G, R, F, c, acc, sa, sbt);
-    const int64_t base = G.offset + block_base(c, 6, N3);
+    constexpr int N2 = N * N, N3 = N * N * N;
+    __shared__ Cells<TC, W> A[N3][64];
+    const TileCell<W> T(G, lane_tile(blockIdx.x, gridDim.x, plane_tiles<N, TS, W>(G)));
+    Cells<TC, W> out[N2];
+    tile_sipg<N, TS, TC, W, 6, HERM>(u, G, R, T, A, out);
+    if (!T.valid) return;
+    TS* tb = t + G.offset + block_base(T.c, 6, N3) + (static_cast<int64_t>(T.w * N2) << 6);
 #pragma unroll
-    for (int e = 0; e < N3; ++e) {
-        const int64_t o = base + (static_cast<int64_t>(e) << 6);
-        t[o] = static_cast<TS>(acc[e]);
-    }
+    for (int e = 0; e < N2; ++e) st_cells<false>(tb + (e << 6), out[e]);
 }
 
 // u = omega D^{-1} b: the first Chebyshev update from u = 0 (no operator
-// application), the block inverse in precision TI.
+// application), the block inverse (E holds omega) in precision TI.
 template <int N, typename TI, typename TS>
-__global__ __launch_bounds__(64, 2) void k_mg_jacobi0(const TS* __restrict__ b, TS* __restrict__ u,
-                                                    MeshArgs G, Eig<N, TI> E, double omega,
-                                                    const PcgState* __restrict__ st) {
+__global__ __launch_bounds__(64 * N, 4) void k_mg_jacobi0(const TS* __restrict__ b, TS* __restrict__ u, MeshArgs G,
+                                                          TileInv<N, TI> E, const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
-    constexpr int N3 = N * N * N;
-    const int64_t c = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;
-    if (c >= G.ncells) return;
-    const int64_t base = G.offset + block_base(c, 6, N3);
-    TI v[N3];
+    constexpr int N2 = N * N, N3 = N * N * N;
+    __shared__ Cells<TI, 1> A[N3][64];
+    const TileCell<1> T(G, blockIdx.x);
+    const int64_t base = G.offset + block_base(T.c, 6, N3) + (static_cast<int64_t>(T.w * N2) << 6);
+    Cells<TI, 1> v[N2];
 #pragma unroll
-    for (int e = 0; e < N3; ++e) v[e] = static_cast<TI>(b[base + (static_cast<int64_t>(e) << 6)]);
-    lane_fdm_inplace<N, TI>(v, E, static_cast<TI>(G.sx), static_cast<TI>(G.sy), static_cast<TI>(G.sz));
+    for (int e = 0; e < N2; ++e) v[e].v[0] = static_cast<TI>(b[base + (e << 6)]);
+    tile_fdm<N, TI, 1>(E, T, A, v);
+    if (!T.valid) return;
 #pragma unroll
-    for (int e = 0; e < N3; ++e)
-        u[base + (static_cast<int64_t>(e) << 6)] = static_cast<TS>(omega * static_cast<double>(v[e]));
+    for (int e = 0; e < N2; ++e) u[base + (e << 6)] = static_cast<TS>(v[e].v[0]);
 }
 
 // One Chebyshev update in a single pass (the factorized form: no residual
-// vector is stored): u_out = u_in + omega D^{-1} (b - A u_in) for the lane's
-// cell, A u_in from the cell and its six neighbours, the block inverse in
-// precision TI on the residual registers.  u_out must not alias u_in (other
-// lanes still read u_in).
-template <int N, typename TI, bool HERM, typename TS>
-__global__ __launch_bounds__(64, (mg_lane_waves<TS, HERM, TI>())) void k_mg_smooth(const TS* __restrict__ b, const TS* __restrict__ uin,
-                                                   TS* __restrict__ uout, MeshArgs G, Pair<N, MgTC<TS>> R,
-                                                   FaceRef<N, MgTC<TS>> F, Eig<N, TI> E, double omega,
-                                                   const PcgState* __restrict__ st) {
+// vector is stored): u_out = u_in + omega D^{-1} (b - A u_in) for the
+// workgroup's cells, A u_in from the cells and their six neighbours, the block
+// inverse (E holds omega) in precision TI on the residual planes.  u_out must
+// not alias u_in (other workgroups still read u_in).
+template <int N, typename TI, bool HERM, typename TS, int W = 1>
+__global__ __launch_bounds__(64 * N, (tile_waves<N, MgTC<TS>, W>())) void k_mg_smooth(
+    const TS* __restrict__ b, const TS* __restrict__ uin, TS* __restrict__ uout, MeshArgs G, TileTab<N, MgTC<TS>, HERM> R,
+    TileInv<N, TI> E, const PcgState* __restrict__ st) {
     using TC = MgTC<TS>;
     if (done_flag(st)) return;
-    constexpr int N3 = N * N * N;
-    __shared__ TC sa[N * N][64], sbt[N * N][64];
-    const int64_t c = static_cast<int64_t>(lane_tile(blockIdx.x, gridDim.x, plane_tiles<N, TS, HERM>(G))) * 64 + threadIdx.x;
-    if (c >= G.ncells) return;
-    TC acc[N3];
-    sipg_cell<N, TS, TC, -1, HERM>(uin, G, R, F, c, acc, sa, sbt);
-    const int64_t base = G.offset + block_base(c, 6, N3);
-    TI v[N3];
+    constexpr int N2 = N * N, N3 = N * N * N;
+    constexpr size_t kBytes = N3 * 64 * W * (sizeof(TC) > sizeof(TI) ? sizeof(TC) : sizeof(TI));
+    __shared__ __align__(16) char lds[kBytes];
+    const TileCell<W> T(G, lane_tile(blockIdx.x, gridDim.x, plane_tiles<N, TS, W>(G)));
+    Cells<TC, W> out[N2];
+    tile_sipg<N, TS, TC, W, 6, HERM>(uin, G, R, T, reinterpret_cast<Cells<TC, W>(*)[64]>(lds), out);
+    const int64_t base = G.offset + block_base(T.c, 6, N3) + (static_cast<int64_t>(T.w * N2) << 6);
+    Cells<TI, W> v[N2];
 #pragma unroll
-    for (int e = 0; e < N3; ++e)
-        v[e] = static_cast<TI>(static_cast<TC>(b[base + (static_cast<int64_t>(e) << 6)]) - acc[e]);
-    lane_fdm_inplace<N, TI>(v, E, static_cast<TI>(G.sx), static_cast<TI>(G.sy), static_cast<TI>(G.sz));
+    for (int e = 0; e < N2; ++e) {
+        const Cells<TC, W> bv = ld_cells<TC, W>(b + base + (e << 6));
 #pragma unroll
-    for (int e = 0; e < N3; ++e) {
-        const int64_t o = base + (static_cast<int64_t>(e) << 6);
-        uout[o] = static_cast<TS>(fma(omega, static_cast<double>(v[e]), static_cast<double>(uin[o])));
+        for (int k = 0; k < W; ++k) v[e].v[k] = static_cast<TI>(bv.v[k] - out[e].v[k]);
+    }
+    // the planes of the two element types do not coincide
+    if constexpr (sizeof(TC) != sizeof(TI)) tile_sync();
+    tile_fdm<N, TI, W>(E, T, reinterpret_cast<Cells<TI, W>(*)[64]>(lds), v);
+    if (!T.valid) return;
+#pragma unroll
+    for (int e = 0; e < N2; ++e) {
+        Cells<double, W> uv = ld_cells<double, W>(uin + base + (e << 6));
+#pragma unroll
+        for (int k = 0; k < W; ++k) uv.v[k] += static_cast<double>(v[e].v[k]);
+        st_cells<false>(uout + base + (e << 6), uv);
     }
 }
 
@@ -768,30 +762,44 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
                            L.G.logB, st);
         return check_launch("coarse solve");
     }
-    Pair<N, MgTC<TS>> R;
-    FaceRef<N, MgTC<TS>> F;
-    sipg_tables<N, MgTC<TS>>(plan, false, R, F);
-    Eig<N, TI> E;
-    for (int i = 0; i < N * N; ++i) E.s[i] = static_cast<TI>(plan.ref[N].S[i]);
-    for (int i = 0; i < N; ++i) E.lam[i] = static_cast<TI>(plan.ref[N].lam[i]);
+    const TileTab<N, MgTC<TS>, HERM> R = tile_tab<N, MgTC<TS>, HERM>(plan, false);
+    TileInv<N, TI> E[3];
+    for (int j = 0; j < 3; ++j) E[j] = tile_inv<N, TI>(plan.ref[N], L.G, m->omega[j]);
     ProlTab<N> P, PT;
     for (int i = 0; i < N * N; ++i) P.p[0][i] = plan.ref[N].P0[i], P.p[1][i] = plan.ref[N].P1[i];
     for (int c = 0; c < 2; ++c)
         for (int i = 0; i < N; ++i)
             for (int j = 0; j < N; ++j) PT.p[c][i * N + j] = P.p[c][j * N + i];
+    const bool pairs = tile_pairs(L.G, sizeof(TS), reinterpret_cast<uintptr_t>(b) % 16 == 0 &&
+                                                       reinterpret_cast<uintptr_t>(u) % 16 == 0);
     // Chebyshev updates ping-pong between u and the level's scratch t; the
     // prolongation writes out of place so that the last update lands in u.
     auto step = [&](const TS* from, TS* to, int j) {
-        hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS>), dim3(grid), dim3(64), 0, s, b, from, to, L.G, R, F, E,
-                           m->omega[j], st);
+        if constexpr (sizeof(TS) == 8) {
+            if (pairs) {
+                hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS, 2>), dim3(tile_grid(L.G, 2)), dim3(64, N), 0, s, b,
+                                   from, to, L.G, R, E[j], st);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS>), dim3(grid), dim3(64, N), 0, s, b, from, to, L.G, R, E[j],
+                           st);
     };
-    hipLaunchKernelGGL((k_mg_jacobi0<N, TI, TS>), dim3(grid), dim3(64), 0, s, b, u, L.G, E, m->omega[0], st);
+    hipLaunchKernelGGL((k_mg_jacobi0<N, TI, TS>), dim3(grid), dim3(64, N), 0, s, b, u, L.G, E[0], st);
     step(u, Lt, 1);
     step(Lt, u, 2);
     const MgLevel& C = m->lv[l + 1];
     TS* Cb = static_cast<TS*>(C.b);
     TS* Cu = static_cast<TS*>(C.u);
-    hipLaunchKernelGGL((k_mg_apply<N, HERM, TS>), dim3(grid), dim3(64), 0, s, u, Lt, L.G, R, F, st);
+    bool wide = false;
+    if constexpr (sizeof(TS) == 8) {
+        wide = pairs;
+        if (wide)
+            hipLaunchKernelGGL((k_mg_apply<N, HERM, TS, 2>), dim3(tile_grid(L.G, 2)), dim3(64, N), 0, s, u, Lt, L.G,
+                               R, st);
+    }
+    if (!wide)
+        hipLaunchKernelGGL((k_mg_apply<N, HERM, TS>), dim3(grid), dim3(64, N), 0, s, u, Lt, L.G, R, st);
     hipLaunchKernelGGL((k_mg_restrict<N, TS>), dim3(static_cast<unsigned>((C.G.ncells + 63) / 64)), dim3(64), 0, s, b,
                        Lt, Cb, L.G, C.G, PT, st);
     tp_status stt = check_launch("level transfer");
@@ -925,6 +933,7 @@ tp_status coarse_probe_n(const tp_mg* m, std::vector<double>& A) {
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&pu), vb);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&pt), vb);
     tp_status st = e == hipSuccess ? TP_OK : hip_error(e, "coarse probe vectors");
+    bool herm = false;
     // column j = A e_j, with pu = e_j as the probe
     for (int64_t j = 0; st == TP_OK && j < n0; ++j) {
         st = launch_fill(pu, L.elems, TP_F64, 0, true, nullptr);
@@ -936,9 +945,19 @@ tp_status coarse_probe_n(const tp_mg* m, std::vector<double>& A) {
             st = hip_error(e, "coarse probe");
             break;
         }
-        if constexpr (N <= kLaneMaxN)
-            hipLaunchKernelGGL((k_mg_apply<N, false, double>), dim3(grid), dim3(64), 0, nullptr, pu, pt, L.G, R, F,
-                               static_cast<const PcgState*>(nullptr));
+        if constexpr (N <= kLaneMaxN) {
+            const PcgState* none = nullptr;
+            if constexpr (N == 4) {
+                if (plan.basis == TP_BASIS_HERMITE) {
+                    hipLaunchKernelGGL((k_mg_apply<N, true, double>), dim3(grid), dim3(64, N), 0, nullptr, pu, pt, L.G,
+                                       tile_tab<N, double, true>(plan, false), none);
+                    herm = true;
+                }
+            }
+            if (!herm)
+                hipLaunchKernelGGL((k_mg_apply<N, false, double>), dim3(grid), dim3(64, N), 0, nullptr, pu, pt, L.G,
+                                   tile_tab<N, double, false>(plan, false), none);
+        }
         else
             hipLaunchKernelGGL((k_mg_apply_wave<N, false>), dim3(static_cast<unsigned>(L.G.ncells)), dim3(64), 0,
                                nullptr, pu, pt, L.G, reinterpret_cast<const double*>(eo_table(plan, N, EO_APPLY_A, 0)),

@@ -21,6 +21,7 @@
 #include <cmath>
 #include <new>
 
+#include "lane.h"
 #include "sipg.h"
 
 namespace tpfdm {
@@ -29,31 +30,36 @@ namespace {
 
 __device__ __forceinline__ bool finite(double v) { return v == v && v <= 1.7976931348623157e308 && v >= -1.7976931348623157e308; }
 
-// 1.  q = A p, partial (p, q) per workgroup (HERM: the two-layer face
-// terms of the Hermite-type basis).
-template <int N, int LB, bool HERM = false>
-__global__ __launch_bounds__(64, 2) void k_pcg_aq(const double* __restrict__ p, double* __restrict__ q, MeshArgs G,
-                                                Pair<N, double> R, FaceRef<N, double> F,
-                                                const PcgState* __restrict__ st, double* __restrict__ part) {
+// 1.  q = A p, partial (p, q) per workgroup of 64 W cells (HERM: the
+// two-layer face terms of the Hermite-type basis).
+template <int N, int W, int LB, bool HERM>
+__global__ __launch_bounds__(64 * N, (tile_waves<N, double, W>())) void k_pcg_aq(const double* __restrict__ p,
+                                                                                 double* __restrict__ q, MeshArgs G,
+                                                                                 TileTab<N, double, HERM> R,
+                                                                                 const PcgState* __restrict__ st,
+                                                                                 double* __restrict__ part) {
     if (st->done) return;
-    constexpr int N3 = N * N * N;
-    __shared__ double sa[N * N][64], sbt[N * N][64];
-    const int64_t c = static_cast<int64_t>(lane_tile(blockIdx.x, gridDim.x, plane_tiles<N, double, HERM>(G))) * 64 + threadIdx.x;
+    constexpr int N2 = N * N, N3 = N * N * N;
+    __shared__ Cells<double, W> A[N3][64];
+    __shared__ double red[N];
+    const TileCell<W> T(G, lane_tile(blockIdx.x, gridDim.x, plane_tiles<N, double, W>(G)));
+    Cells<double, W> out[N2];
+    tile_sipg<N, double, double, W, LB, HERM>(p, G, R, T, A, out);
     const int lb = LB >= 0 ? LB : G.logB;
+    const int64_t base = G.offset + block_base(T.c, lb, N3) + (static_cast<int64_t>(T.w * N2) << lb);
     double dot = 0.0;
-    if (c < G.ncells) {
-        double acc[N3];
-        sipg_cell<N, double, double, LB, HERM>(p, G, R, F, c, acc, sa, sbt);
-        const int64_t base = G.offset + block_base(c, lb, N3);
+    if (T.valid) {
 #pragma unroll
-        for (int e = 0; e < N3; ++e) {
+        for (int e = 0; e < N2; ++e) {
             const int64_t o = base + (static_cast<int64_t>(e) << lb);
-            q[o] = acc[e];
-            dot = fma(acc[e], p[o], dot);
+            st_cells<false>(q + o, out[e]);
+            const Cells<double, W> pv = ld_cells<double, W>(p + o);
+#pragma unroll
+            for (int k = 0; k < W; ++k) dot = fma(out[e].v[k], pv.v[k], dot);
         }
     }
-    dot = wave_sum(dot);
-    if (threadIdx.x == 0) part[blockIdx.x] = dot;
+    dot = tile_sum<N>(dot, red);
+    if (threadIdx.x == 0 && threadIdx.y == 0) part[blockIdx.x] = dot;
 }
 
 // Fixed-order sum of count partials by one 256-thread workgroup.
@@ -644,6 +650,8 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
     // 16-byte pencils for the wave body: block-contiguous layout (the
     // solver's vectors are allocation-aligned)
     const bool vp = g.logB == 0 && (N * sizeof(double)) % 16 == 0;
+    const bool pairs = kLane && tile_pairs(G, sizeof(double), true);
+    const int64_t aqcnt = pairs ? tile_grid(G, 2) : cnt;   // partials of (p, q)
     // the wave kernels of the Hermite-type basis use sign-flipped tables and
     // endpoint derivatives (see wave_sipg_cell)
     const bool herm = !kLane && plan.basis == TP_BASIS_HERMITE;
@@ -719,15 +727,25 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
         if (e == hipSuccess) {
             for (int i = 0; i < chunk; ++i) {
                 if constexpr (kLane) {
-                    bool herm = false;
-                    if constexpr (N == 4) herm = plan.basis == TP_BASIS_HERMITE;
-                    if (herm) {
-                        if constexpr (N == 4)
-                            hipLaunchKernelGGL((k_pcg_aq<N, LB, true>), dim3(nwg), dim3(64), 0, cs, s->p, s->q, G, R,
-                                               F, s->st, s->part);
-                    } else {
-                        hipLaunchKernelGGL((k_pcg_aq<N, LB>), dim3(nwg), dim3(64), 0, cs, s->p, s->q, G, R, F, s->st,
+                    const dim3 wg(64, N), gr1(tile_grid(G, 1)), gr2(tile_grid(G, 2));
+                    auto aq = [&](auto Hc) {
+                        constexpr bool H = decltype(Hc)::value;
+                        const TileTab<N, double, H> R = tile_tab<N, double, H>(plan, false);
+                        if constexpr (LB == 6) {
+                            if (pairs) {
+                                hipLaunchKernelGGL((k_pcg_aq<N, 2, LB, H>), gr2, wg, 0, cs, s->p, s->q, G, R,
+                                                   s->st, s->part);
+                                return;
+                            }
+                        }
+                        hipLaunchKernelGGL((k_pcg_aq<N, 1, LB, H>), gr1, wg, 0, cs, s->p, s->q, G, R, s->st,
                                            s->part);
+                    };
+                    if constexpr (N == 4) {
+                        if (plan.basis == TP_BASIS_HERMITE) aq(std::true_type{});
+                        else aq(std::false_type{});
+                    } else {
+                        aq(std::false_type{});
                     }
                 } else if (herm) {
                     if (vp)
@@ -742,7 +760,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                 else
                     hipLaunchKernelGGL((k_pcg_aq_wave<N, false, false>), dim3(nwg), dim3(64), 0, cs, s->p, s->q, G,
                                        tabA, F, s->st, s->part);
-                hipLaunchKernelGGL(k_pcg_reduce_alpha, dim3(1), dim3(256), 0, cs, s->part, cnt, s->st);
+                hipLaunchKernelGGL(k_pcg_reduce_alpha, dim3(1), dim3(256), 0, cs, s->part, aqcnt, s->st);
                 if (s->mg) {
                     if constexpr (!kLane) {
                         if (vp)

@@ -5,21 +5,22 @@ namespace tpfdm {
 
 namespace {
 
-// One cell per lane (n <= 4).  The cell's own block is read with cached
-// loads (it is also a face source of its neighbours); v is streamed out.
-template <int N, typename TS, typename TC, bool NT, int LB, bool HERM = false>
-__global__ __launch_bounds__(64, 2) void k_sipg_lane(const TS* __restrict__ u, TS* __restrict__ v, MeshArgs G,
-                                                   Pair<N, TC> R, FaceRef<N, TC> F) {
-    constexpr int N3 = N * N * N;
-    __shared__ TC sa[N * N][64], sbt[N * N][64];
-    const int64_t c = static_cast<int64_t>(lane_tile(blockIdx.x, gridDim.x, plane_tiles<N, TS, HERM>(G))) * 64 + threadIdx.x;
-    if (c >= G.ncells) return;
-    TC acc[N3];
-    sipg_cell<N, TS, TC, LB, HERM>(u, G, R, F, c, acc, sa, sbt);
+// 64 W cells per workgroup of N waves (n <= 4).  u is read with cached
+// loads (a block is also a face source of its neighbours); v is streamed out.
+template <int N, typename TS, typename TC, int W, bool NT, int LB, bool HERM = false>
+__global__ __launch_bounds__(64 * N, (tile_waves<N, TC, W>())) void k_sipg_tile(const TS* __restrict__ u,
+                                                                                TS* __restrict__ v, MeshArgs G,
+                                                                                TileTab<N, TC, HERM> R) {
+    constexpr int N2 = N * N, N3 = N * N * N;
+    __shared__ Cells<TC, W> A[N3][64];
+    const TileCell<W> T(G, lane_tile(blockIdx.x, gridDim.x, plane_tiles<N, TS, W>(G)));
+    Cells<TC, W> out[N2];
+    tile_sipg<N, TS, TC, W, LB, HERM>(u, G, R, T, A, out);
+    if (!T.valid) return;
     const int lb = LB >= 0 ? LB : G.logB;
-    TS* vb = v + G.offset + block_base(c, lb, N3);
+    TS* vb = v + G.offset + block_base(T.c, lb, N3) + (static_cast<int64_t>(T.w * N2) << lb);
 #pragma unroll
-    for (int q = 0; q < N3; ++q) stv<NT>(vb + (static_cast<int64_t>(q) << lb), acc[q]);
+    for (int q = 0; q < N2; ++q) st_cells<NT>(vb + (static_cast<int64_t>(q) << lb), out[q]);
 }
 
 // One cell per wave (n >= 5); HERM: the Hermite-type basis.
@@ -59,34 +60,25 @@ tp_status check_launch(const char* what) {
     if (e != hipSuccess) return hip_error(e, what);
     return TP_OK;
 }
-template <int N, typename TS, typename TC>
-tp_status sipg_lane_n(const Plan& plan, const MeshArgs& G, bool face_only, const void* u, void* v, hipStream_t s) {
-    Pair<N, TC> R;
-    FaceRef<N, TC> F;
-    sipg_tables<N, TC>(plan, face_only, R, F);
-    const unsigned grid = static_cast<unsigned>((G.ncells + 63) / 64);
+template <int N, typename TS, typename TC, bool HERM>
+tp_status sipg_tile_n(const Plan& plan, const MeshArgs& G, bool face_only, const void* u, void* v, hipStream_t s) {
+    const TileTab<N, TC, HERM> R = tile_tab<N, TC, HERM>(plan, face_only);
     const TS* ui = static_cast<const TS*>(u);
     TS* vo = static_cast<TS*>(v);
-    if constexpr (N == 4) {   // the Hermite-type basis: two-layer face terms
-        if (plan.basis == TP_BASIS_HERMITE) {
-            if (G.logB == 6)
-                hipLaunchKernelGGL((k_sipg_lane<N, TS, TC, true, 6, true>), dim3(grid), dim3(64), 0, s, ui, vo, G, R,
-                                   F);
-            else if (lane_whole_lines<TS>(G.logB))
-                hipLaunchKernelGGL((k_sipg_lane<N, TS, TC, true, -1, true>), dim3(grid), dim3(64), 0, s, ui, vo, G,
-                                   R, F);
-            else
-                hipLaunchKernelGGL((k_sipg_lane<N, TS, TC, false, -1, true>), dim3(grid), dim3(64), 0, s, ui, vo, G,
-                                   R, F);
-            return check_launch("SIPG apply launch");
-        }
+    const bool aligned = reinterpret_cast<uintptr_t>(u) % 16 == 0 && reinterpret_cast<uintptr_t>(v) % 16 == 0;
+    const dim3 wg(64, N);
+    if (tile_pairs(G, sizeof(TS), aligned)) {
+        if constexpr (sizeof(TS) == 8)
+            hipLaunchKernelGGL((k_sipg_tile<N, TS, TC, 2, true, 6, HERM>), dim3(tile_grid(G, 2)), wg, 0, s, ui, vo, G,
+                               R);
+    } else if (G.logB == 6) {
+        hipLaunchKernelGGL((k_sipg_tile<N, TS, TC, 1, true, 6, HERM>), dim3(tile_grid(G, 1)), wg, 0, s, ui, vo, G, R);
+    } else if (lane_whole_lines<TS>(G.logB)) {
+        hipLaunchKernelGGL((k_sipg_tile<N, TS, TC, 1, true, -1, HERM>), dim3(tile_grid(G, 1)), wg, 0, s, ui, vo, G, R);
+    } else {
+        hipLaunchKernelGGL((k_sipg_tile<N, TS, TC, 1, false, -1, HERM>), dim3(tile_grid(G, 1)), wg, 0, s, ui, vo, G,
+                           R);
     }
-    if (G.logB == 6)
-        hipLaunchKernelGGL((k_sipg_lane<N, TS, TC, true, 6>), dim3(grid), dim3(64), 0, s, ui, vo, G, R, F);
-    else if (lane_whole_lines<TS>(G.logB))
-        hipLaunchKernelGGL((k_sipg_lane<N, TS, TC, true, -1>), dim3(grid), dim3(64), 0, s, ui, vo, G, R, F);
-    else
-        hipLaunchKernelGGL((k_sipg_lane<N, TS, TC, false, -1>), dim3(grid), dim3(64), 0, s, ui, vo, G, R, F);
     return check_launch("SIPG apply launch");
 }
 
@@ -121,9 +113,11 @@ template <typename TS, typename TC>
 tp_status sipg_dispatch(const Plan& plan, const MeshArgs& G, int n, bool face_only, const void* u, void* v,
                         hipStream_t s) {
     switch (n) {
-        case 2: return sipg_lane_n<2, TS, TC>(plan, G, face_only, u, v, s);
-        case 3: return sipg_lane_n<3, TS, TC>(plan, G, face_only, u, v, s);
-        case 4: return sipg_lane_n<4, TS, TC>(plan, G, face_only, u, v, s);
+        case 2: return sipg_tile_n<2, TS, TC, false>(plan, G, face_only, u, v, s);
+        case 3: return sipg_tile_n<3, TS, TC, false>(plan, G, face_only, u, v, s);
+        case 4:   // the Hermite-type basis has n >= 4: two-layer face terms
+            return plan.basis == TP_BASIS_HERMITE ? sipg_tile_n<4, TS, TC, true>(plan, G, face_only, u, v, s)
+                                                  : sipg_tile_n<4, TS, TC, false>(plan, G, face_only, u, v, s);
         case 5: return sipg_wave_n<5, TC>(plan, G, face_only, u, v, s);
         case 6: return sipg_wave_n<6, TC>(plan, G, face_only, u, v, s);
         case 7: return sipg_wave_n<7, TC>(plan, G, face_only, u, v, s);
