@@ -446,19 +446,6 @@ __device__ __forceinline__ void eo_apply_regs(const Pencil<N>& pc, const TC (&x)
     wave_sync();
 }
 
-// dst = A src entirely in LDS (dst may alias src); t1, t2 scratch slabs.
-template <int N, typename TC>
-__device__ __forceinline__ void eo_apply_lds(const Pencil<N>& pc, const TC* src, TC* dst, TC* t1, TC* t2,
-                                             const TC* ME, const TC* MO, const TC* PE, const TC* PO, TC sx, TC sy,
-                                             TC sz) {
-    using L = Slab<N>;
-    TC x[N];
-    if (pc.act)
-#pragma unroll
-        for (int k = 0; k < N; ++k) x[k] = src[L::at(pc.pa, pc.pb, k)];
-    eo_apply_regs<N, TC>(pc, x, dst, t1, t2, ME, MO, PE, PO, sx, sy, sz);
-}
-
 // r <- D^{-1} r with the lane's z-pencil of r in registers on entry and on
 // return, through the LDS slab (each phase updates its own pencils).
 template <int N, typename TC>

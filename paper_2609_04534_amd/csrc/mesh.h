@@ -49,35 +49,39 @@ __device__ __forceinline__ XcdRange xcd_range(unsigned b, unsigned nwg) {
     const unsigned q = nwg / 8, r = nwg % 8, x = b % 8;
     return {x * q + (x < r ? x : r), q + (x < r ? 1u : 0u), b / 8};
 }
-// Tile of workgroup b in that order.
-__device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned nwg) {
-    const XcdRange x = xcd_range(b, nwg);
-    return x.first + x.place;
-}
-
-// Tile of workgroup b for the one-cell-per-lane kernels of a mesh plan (about
-// S tiles per x-plane of cells).  Each XCD walks its range in groups of
-// kLaneSweep consecutive tiles carried through the range's rows of S tiles:
-// a tile's x neighbours then come kLaneSweep tiles apart in the visiting
-// order instead of S, and are still in the XCD's L2 when the second of them
-// reads them.  A bijection on [0, nwg): the last group of a row is S mod
-// kLaneSweep wide when kLaneSweep does not divide S; the part of the range
-// past its last whole row, and S = 0, keep the plain order.
-constexpr unsigned kLaneSweep = 8;
-
-__device__ __forceinline__ unsigned lane_tile(unsigned b, unsigned nwg, unsigned S) {
+// Tile of workgroup b on a mesh with about S tiles per x-plane of cells: each
+// XCD walks its range in groups of SW consecutive tiles carried through the
+// range's rows of S tiles.  A tile's x neighbours then come SW tiles apart in
+// the visiting order instead of S, and are still in the XCD's L2 when the
+// second of them reads them.  A bijection on [0, nwg): the last group of a
+// row is S mod SW wide when SW does not divide S; the part of the range past
+// its last whole row, and S = 0, keep the plain order.
+__device__ __forceinline__ unsigned sweep_tile(unsigned b, unsigned nwg, unsigned S, unsigned SW) {
     const XcdRange x = xcd_range(b, nwg);
     const unsigned l = x.place;
     if (S == 0) return x.first + l;
     const unsigned R = x.count / S;
     if (R < 2 || l >= R * S) return x.first + l;
-    const unsigned full = (S / kLaneSweep) * kLaneSweep * R;   // tiles in whole-width groups
+    const unsigned full = (S / SW) * SW * R;   // tiles in whole-width groups
     if (l < full) {
-        const unsigned chunk = l / (kLaneSweep * R), r = (l / kLaneSweep) % R, g = l % kLaneSweep;
-        return x.first + r * S + chunk * kLaneSweep + g;
+        const unsigned chunk = l / (SW * R), r = (l / SW) % R, g = l % SW;
+        return x.first + r * S + chunk * SW + g;
     }
-    const unsigned w = S % kLaneSweep, e = l - full;          // w > 0 here
+    const unsigned w = S % SW, e = l - full;          // w > 0 here
     return x.first + (e / w) * S + (S - w) + e % w;
+}
+
+// The tile kernels (n <= 4) sweep groups of 8 tiles.
+constexpr unsigned kLaneSweep = 8;
+__device__ __forceinline__ unsigned lane_tile(unsigned b, unsigned nwg, unsigned S) {
+    return sweep_tile(b, nwg, S, kLaneSweep);
+}
+
+// The one-cell-per-wave kernels (n >= 5) sweep groups of 192 cells (n = 8 in
+// FP64 on 48^3 cells: 397 us in plain order, 374, 367, 368 and 373 us with 48,
+// 192, 384 and 768; FP32 and smaller n within 2%).
+__device__ __forceinline__ unsigned wave_tile(unsigned b, unsigned nwg, const MeshArgs& G) {
+    return sweep_tile(b, nwg, static_cast<unsigned>(G.my) * static_cast<unsigned>(G.mz), 192);
 }
 
 // Row length S for lane_tile: the whole tiles of 64 W cells in an x-plane of
@@ -126,16 +130,6 @@ void sipg_tables(const Plan& plan, bool face_only, Pair<N, TC>& R, FaceRef<N, TC
         F.g1[i] = static_cast<TC>(ref.g1[i]);
     }
     F.sigma = static_cast<TC>(plan.penalty_C * (N - 1) * N);
-}
-
-// The wave kernels of the Hermite-type basis work in the sign-flipped
-// coefficients (see wave_sipg_cell): endpoint derivatives D g.
-template <int N, typename T>
-void flip_face_ref(FaceRef<N, T>& F) {
-    for (int k = 0; k < N; ++k) {
-        F.g0[k] = static_cast<T>(hermite_sign(N, k)) * F.g0[k];
-        F.g1[k] = static_cast<T>(hermite_sign(N, k)) * F.g1[k];
-    }
 }
 
 }  // namespace tpfdm

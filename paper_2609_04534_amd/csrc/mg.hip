@@ -314,13 +314,13 @@ __device__ __forceinline__ const T* wave_row_tables(T (&regs)[sizeof(T) == 8 ? 1
 template <int N, bool VP, typename T = double>
 __global__ __launch_bounds__(64, 2) void k_mg_apply_wave(const T* __restrict__ u, T* __restrict__ t,
                                                        MeshArgs G, const T* __restrict__ tab,
-                                                       FaceRef<N, T> F, const PcgState* __restrict__ st) {
+                                                       WaveFace<N, T> F, const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
     constexpr int TAB = 2 * (EOShape<N>::SE + EOShape<N>::SO);
     __shared__ WaveLds<N, T> L;
     T regs[sizeof(T) == 8 ? 1 : TAB];
     const T* tb = wave_row_tables<T, TAB>(regs, tab);
-    const int64_t c = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t c = wave_tile(blockIdx.x, gridDim.x, G);
     T y[N];
     wave_sipg_cell<N, T, VP, false>(u, G, tb, F, c, L, y);
     const Pencil<N> pc(1);
@@ -380,7 +380,7 @@ template <int N, typename TI, bool VP, typename T = double>
 __global__ __launch_bounds__(64, 2) void k_mg_smooth_wave(const T* __restrict__ b,
                                                         const T* __restrict__ uin, T* __restrict__ uout,
                                                         MeshArgs G, const T* __restrict__ tab,
-                                                        FaceRef<N, T> F, const TI* __restrict__ tabS,
+                                                        WaveFace<N, T> F, const TI* __restrict__ tabS,
                                                         double omega, const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
     using SL = Slab<N>;
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(64, 2) void k_mg_smooth_wave(const T* __restrict__ 
     for (int e = threadIdx.x; e < TABM + N; e += 64) stab[e] = tabS[e];
     T regs[sizeof(T) == 8 ? 1 : TAB];
     const T* tb = wave_row_tables<T, TAB>(regs, tab);
-    const int64_t c = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t c = wave_tile(blockIdx.x, gridDim.x, G);
     const Pencil<N> pc(1);
     const T* bb = b + G.offset + block_base(c, G.logB, N * N * N);
     // FP32: the lane's x-pencil of b and z-pencil of u_in are loaded before
@@ -830,11 +830,7 @@ tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const 
                            L.G.offset, L.G.logB, st);
         return check_launch("coarse solve");
     }
-    FaceRef<N, TS> F;
-    {
-        Pair<N, TS> R;
-        sipg_tables<N, TS>(plan, false, R, F);
-    }
+    const WaveFace<N, TS> F = wave_face<N, TS>(plan);
     const TS* tabA = reinterpret_cast<const TS*>(eo_table(plan, N, EO_APPLY_A, sizeof(TS) == 8 ? 0 : 1));
     const TI* tabS = reinterpret_cast<const TI*>(eo_table(plan, N, EO_INV, sizeof(TI) == 8 ? 0 : 1));
     ProlTab<N> P, PT;
@@ -919,9 +915,7 @@ template <int N>
 tp_status coarse_probe_n(const tp_mg* m, std::vector<double>& A) {
     const Plan& plan = *m->plan;
     const MgLevel& L = m->lv.back();
-    Pair<N, double> R;
-    FaceRef<N, double> F;
-    sipg_tables<N, double>(plan, false, R, F);
+    const WaveFace<N, double> F = wave_face<N, double>(plan);
     constexpr int N3 = N * N * N;
     const int64_t n0 = m->n0;
     A.assign(static_cast<size_t>(n0 * n0), 0.0);
@@ -982,11 +976,7 @@ template <int N>
 tp_status coarse_probe_deg(const tp_mg* m, std::vector<double>& A) {
     const Plan& plan = *m->plan;
     const MgLevel& L = m->lv.back();
-    FaceRef<N, double> F;
-    {
-        Pair<N, double> R;
-        sipg_tables<N, double>(plan, false, R, F);
-    }
+    const WaveFace<N, double> F = wave_face<N, double>(plan);
     const double* tabA = reinterpret_cast<const double*>(eo_table(plan, N, EO_APPLY_A, 0));
     const DegTab<N> E = deg_table<N>();
     const int64_t n0 = m->n0;

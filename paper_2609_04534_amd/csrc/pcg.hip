@@ -326,7 +326,7 @@ __global__ __launch_bounds__(64) void k_pcg_axpy(double* __restrict__ x, double*
 template <int N, bool VP, bool HERM>
 __global__ __launch_bounds__(64, 2) void k_pcg_aq_wave(const double* __restrict__ p, double* __restrict__ q,
                                                      MeshArgs G, const double* __restrict__ tab,
-                                                     FaceRef<N, double> F, const PcgState* __restrict__ st,
+                                                     WaveFace<N, double> F, const PcgState* __restrict__ st,
                                                      double* __restrict__ part) {
     if (st->done) return;
     constexpr int TAB = 2 * (EOShape<N>::SE + EOShape<N>::SO);
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(64, 2) void k_pcg_aq_wave(const double* __restrict_
     // the FP64 tables are read at wave-uniform global addresses (scalar
     // loads), not from registers or LDS
     static_assert(TAB > 0, "table");
-    const int64_t c = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t c = wave_tile(blockIdx.x, gridDim.x, G);
     double y[N];
     wave_sipg_cell<N, double, VP, HERM>(p, G, tab, F, c, L, y);
     const Pencil<N> pc(1);
@@ -637,9 +637,6 @@ template <int N, typename TI, int LB>
 tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const double* b, const double* x,
                       bool x_zero, double rtol, int maxit, int chunk, hipStream_t stream) {
     const MeshArgs G = mesh_args(plan, g);
-    Pair<N, double> R;
-    FaceRef<N, double> F;
-    sipg_tables<N, double>(plan, false, R, F);
     const Eig<N, TI> E = mesh_eig<N, TI>(plan.ref[N]);
     const unsigned nwg = static_cast<unsigned>(s->nwg);
     const int64_t cnt = s->nwg;
@@ -652,11 +649,9 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
     const bool vp = g.logB == 0 && (N * sizeof(double)) % 16 == 0;
     const bool pairs = kLane && tile_pairs(G, sizeof(double), true);
     const int64_t aqcnt = pairs ? tile_grid(G, 2) : cnt;   // partials of (p, q)
-    // the wave kernels of the Hermite-type basis use sign-flipped tables and
-    // endpoint derivatives (see wave_sipg_cell)
+    // (the wave kernels of the Hermite-type basis use sign-flipped tables, see wave_sipg_cell)
     const bool herm = !kLane && plan.basis == TP_BASIS_HERMITE;
-    FaceRef<N, double> Fw = F;
-    if (herm) flip_face_ref<N, double>(Fw);
+    const WaveFace<N, double> F = wave_face<N, double>(plan);
     if (!x_zero) {
         tp_status st = launch_sipg(plan, g, false, x, s->q, TP_F64, stream);
         if (st != TP_OK) return st;
@@ -750,10 +745,10 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                 } else if (herm) {
                     if (vp)
                         hipLaunchKernelGGL((k_pcg_aq_wave<N, true, true>), dim3(nwg), dim3(64), 0, cs, s->p, s->q, G,
-                                           tabA, Fw, s->st, s->part);
+                                           tabA, F, s->st, s->part);
                     else
                         hipLaunchKernelGGL((k_pcg_aq_wave<N, false, true>), dim3(nwg), dim3(64), 0, cs, s->p, s->q,
-                                           G, tabA, Fw, s->st, s->part);
+                                           G, tabA, F, s->st, s->part);
                 } else if (vp)
                     hipLaunchKernelGGL((k_pcg_aq_wave<N, true, false>), dim3(nwg), dim3(64), 0, cs, s->p, s->q, G,
                                        tabA, F, s->st, s->part);

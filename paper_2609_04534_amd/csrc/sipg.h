@@ -46,58 +46,94 @@
 
 namespace tpfdm {
 
-// DoF index of (normal layer k, tangential a, b) for a face normal to axis D
-// (a, b are the two other axes in increasing order).
-template <int N, int D>
-__device__ __forceinline__ constexpr int fq(int k, int a, int b) {
-    return D == 0 ? (k * N + a) * N + b : D == 1 ? (a * N + k) * N + b : (a * N + b) * N + k;
-}
-
 // ============================================================ one cell per wave (n >= 5)
-// The cell's block lives in an LDS slab (Slab<N> layout, one pencil per lane
-// and phase, as in the even-odd wave kernels); the volume product is the
-// even-odd LDS apply with the cell-diagonal P_hat, done first.  The six face
-// terms are slabs over the two tangential indices, kept in the volume
-// product's scratch once that is free: lane (a, b) accumulates alpha and
-// beta of every face from the source block's n values along the normal at
-// (a, b); the tangential mass M (.) M of all twelve slabs runs as two
-// in-place LDS passes of one n-pencil per task (a task owns its row, then
-// its column; 12 n tasks per pass spread over the wave); finally lane (j, k)
-// adds the face terms to its x-pencil of the volume product.
-// The volume product's second scratch slab is the block's own slab s: each
-// lane overwrites only the slab positions it has itself just read (its
-// pencil in the first phase, its x-pencil in the last), so s, one scratch
-// slab and the face slabs are all the LDS a wave needs (10.75 KB at n = 8
-// in FP64: 14 waves per CU instead of 11).
+// The cell's block moves through LDS slabs (Slab<N> layout, one pencil per
+// lane and phase, as in the even-odd wave kernels).  With B_d the 1D operator
+// of axis d including its two faces, the row is
+//   v = B_x a' + M_x b,  a' = M_y M_z u,  b = s_y B_y (M_z u) + s_z M_y (B_z u),
+// where the face part of B_z acts on the lane's own z-pencils (and the
+// neighbours' behind them) before any mass, and the face parts of B_y and
+// B_x, which need the neighbours' values under M_z (and M_y), are carried as
+// four slabs per axis over the two tangential indices: lane (a, b) forms them
+// from the neighbours' n values along the normal, M_z runs on all eight slabs
+// in one pass (8 n row tasks), M_y on the four x slabs, and each lane then
+// adds its four values in the even and odd halves of its y- or x-pencil.
+// (Twelve slabs through both masses and added to the finished row took 28
+// LDS passes of a block against 13 here; the kernel was bound by LDS, 83% of
+// its time at n = 8 in FP64.)
 template <int N, typename T>
 struct WaveLds {
-    static constexpr int kT = 12 * N * N > Slab<N>::size ? 12 * N * N : Slab<N>::size;
-    T s[Slab<N>::size];          // the cell's block, then its volume product (and scratch t2)
-    T t[kT];                     // volume scratch t1, then the twelve face slabs
+    static constexpr int kFace = 8 * N * (N + 1);   // the eight face slabs, rows padded like a block's pencils
+    T s[Slab<N>::size];
+    T t[kFace > Slab<N>::size ? kFace : Slab<N>::size];
 };
+
+// Face tables of the wave rows, with h0 = g0 / 2 (sign-flipped for the
+// Hermite-type basis: g1 = -g0 reversed holds in both): c[1][t] = -h0[t]
+// minus sigma at t = 0 weighs layer t (counted from the face) of a neighbour,
+// c[0][t] = h0[t] the cell's own layers at a boundary face; he and ho are the
+// even and odd halves of h0.
+template <int N, typename T>
+struct WaveFace {
+    T c[2][N];
+    T he[EOShape<N>::HC], ho[EOShape<N>::H];
+};
+
+// What two opposite faces add to a pencil, in its even and odd halves:
+// E_i += he_i bd (+ ad at i = 0), O_i += ho_i bs (+ as at i = 0), with
+// ad, as = (alpha_lower +- alpha_upper) / 2, bd, bs = beta_lower -+ beta_upper.
+template <typename T>
+struct FacePair {
+    T ap, am, bd, bs;
+    __device__ __forceinline__ FacePair(T al, T bl, T ah, T bh)
+        : ap(T(0.5) * (al + ah)), am(T(0.5) * (al - ah)), bd(bl - bh), bs(bl + bh) {}
+    __device__ __forceinline__ FacePair(const T* f, int st) : ap(f[0]), am(f[st]), bd(f[2 * st]), bs(f[3 * st]) {}
+    template <int N>
+    __device__ __forceinline__ void add(const WaveFace<N, T>& F, T s, T (&E)[EOShape<N>::HC],
+                                        T (&O)[EOShape<N>::H]) const {
+        const T sd = s * bd, ss = s * bs;
+        E[0] = fma(s, ap, E[0]);
+        O[0] = fma(s, am, O[0]);
+#pragma unroll
+        for (int i = 0; i < EOShape<N>::HC; ++i) E[i] = fma(F.he[i], sd, E[i]);
+#pragma unroll
+        for (int i = 0; i < EOShape<N>::H; ++i) O[i] = fma(F.ho[i], ss, O[i]);
+    }
+};
+
+// lo = (a of the lower half-wave in lanes 0-31, b of it in lanes 32-63), hi =
+// the same of the upper half-wave.
+__device__ __forceinline__ void half_swap(double a, double b, double& lo, double& hi) {
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    lo = __hiloint2double(h[0], l[0]);
+    hi = __hiloint2double(h[1], l[1]);
+}
 
 // The lane's x-pencil y[i] = (A u)_c at (i, j, k) with (j, k) = (pc.pa,
 // pc.pb), for the active lanes; every lane of the wave must call it.
 // TB: ME | MO | PE | PO (even-odd halves of M_hat and of the cell-diagonal
-// P_hat); F: endpoint derivatives and the reference penalty.
+// P_hat).
 // HERM: the Hermite-type basis.  The even-odd tables then hold the matrices
 // conjugated by D = diag(hermite_sign) (centrosymmetric), so every value is
 // multiplied by its sign s(i) s(j) s(k) on load and on store, and the face
-// terms read only the layers 0, 1, n-2, n-1 along the normal (the others
-// carry no weight: eq. (hermite_traces_3d)).
+// terms read only the two layers next to the face (the others carry no
+// weight: eq. (hermite_traces_3d)).
 template <int N, typename T, bool VP, bool HERM = false>
 __device__ __forceinline__ void wave_sipg_cell(const T* __restrict__ u, const MeshArgs& G, const T* TB,
-                                               const FaceRef<N, T>& F, int64_t c, WaveLds<N, T>& L,
+                                               const WaveFace<N, T>& F, int64_t c, WaveLds<N, T>& L,
                                                T (&y)[N]) {
     using SL = Slab<N>;
     using S = EOShape<N>;
-    constexpr int N3 = N * N * N;
+    constexpr int N3 = N * N * N, HC = S::HC, H = S::H;
+    constexpr int LV = HERM ? 2 : N;               // layers of a face's source that carry weight
+    constexpr int FR = N + 1, FS = N * (N + 1);    // face slab strides: row, slab
     const T* ME = TB;
     const T* MO = TB + S::SE;
     const T* PE = TB + S::SE + S::SO;
     const T* PO = TB + 2 * S::SE + S::SO;
     const Pencil<N> pc(1);
-    const int pa = pc.pa, pb = pc.pb;
+    const int pa = pc.pa, pb = pc.pb, lane = threadIdx.x;
     const T* ub = u + G.offset;
     const int lb = G.logB;
     const uint32_t cu = static_cast<uint32_t>(c);
@@ -106,149 +142,216 @@ __device__ __forceinline__ void wave_sipg_cell(const T* __restrict__ u, const Me
     const uint32_t cy = rr % static_cast<uint32_t>(G.my);
     const uint32_t cx = rr / static_cast<uint32_t>(G.my);
     const T sx = static_cast<T>(G.sx), sy = static_cast<T>(G.sy), sz = static_cast<T>(G.sz);
+    const int64_t syz = static_cast<int64_t>(G.my) * G.mz;
     auto sg = [](int i) { return HERM ? static_cast<T>(hermite_sign(N, i)) : T(1); };
     const T sab = sg(pa) * sg(pb);   // sign of the lane's two tangential indices
-    // --- the cell's own block into the slab, volume product in place
-    if (pc.act) {
-        T x[N];
-        pencil_load<N, VP>(x, ub + block_base(c, lb, N3) + (static_cast<int64_t>((pa * N + pb) * N) << lb), lb);
-#pragma unroll
-        for (int k = 0; k < N; ++k) L.s[SL::at(pa, pb, k)] = HERM ? sab * sg(k) * x[k] : x[k];
-    }
-    wave_sync();
-    eo_apply_lds<N, T>(pc, L.s, L.s, L.t, L.s, ME, MO, PE, PO, sx, sy, sz);   // ends synced
-    // --- face slabs in the free scratch: alpha (2 f) and beta (2 f + 1) of
-    // face f = 2 axis + upper, slab sl at fs + sl n^2
     T* fs = L.t;
-    const int64_t syz = static_cast<int64_t>(G.my) * G.mz;
-    auto face = [&](auto Dc, auto UPc, bool interior, int64_t d, T s) {
-        constexpr int D = decltype(Dc)::value;
+    // alpha and beta of one face from layers v_t counted from the source's
+    // side of the face (rev: the source's last layer is next to the face)
+    auto reduce = [&](const T (&v)[N], bool interior, bool rev, T& al, T& be) {
+        const T* cf = F.c[interior ? 1 : 0];
+        al = cf[0] * v[0];
+#pragma unroll
+        for (int t = 1; t < LV; ++t) al = fma(cf[t], v[t], al);
+        be = rev ? -v[0] : v[0];
+    };
+    // x and y faces: lane (a, b) reads its pencil along the normal (stride ST)
+    auto face = [&](auto STc, auto UPc, bool interior, int64_t d, T& al, T& be) {
+        constexpr int ST = decltype(STc)::value;
         constexpr bool UP = decltype(UPc)::value;
-        constexpr int f = 2 * D + (UP ? 1 : 0);
-        const T* w = ub + block_base(interior ? c + d : c, lb, N3);
-        const bool first = (UP == interior);
-        const T cb0 = first ? T(0.5) * s : T(0);
-        const T cbn = first ? T(0) : T(-0.5) * s;
-        if (pc.act) {
-            // normal to z the n values are the lane's contiguous pencil: one
-            // vector load per 16 bytes when VP
-            T al = T(0), be = T(0);
-            if constexpr (HERM) {
-                // two source layers: 0, 1 when the face is interior at the
-                // upper end or boundary at the lower end, else n-2, n-1
-                // (the weights of the other layers vanish in this basis)
-                const int k0 = first ? 0 : N - 2;
+        const bool rev = UP != interior;
+        const int q0 = (ST == N * N ? pa * N + pb : pa * N * N + pb) + (rev ? (N - 1) * ST : 0);
+        const int step = rev ? -ST : ST;
+        const T* p = ub + block_base(interior ? c + d : c, lb, N3) + (static_cast<int64_t>(q0) << lb);
+        T v[N];
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int k = k0 + t;
-                    T wk = ldc<T>(w + (static_cast<int64_t>(D == 0 ? (k * N + pa) * N + pb
-                                                           : D == 1 ? (pa * N + k) * N + pb
-                                                                    : (pa * N + pb) * N + k) << lb));
-                    wk *= sab * sg(k);
-                    // alpha weight of layer k (as below), selected per lane
-                    T wgt = T(0);
+        for (int t = 0; t < LV; ++t) {
+            v[t] = ldc<T>(p + (static_cast<int64_t>(t * step) << lb));
+            // (layer t from the face: its sign is that of index t or N - 1 - t)
+            if (HERM) v[t] *= sab * (rev ? sg(N - 1 - t) : sg(t));
+        }
+        reduce(v, interior, rev, al, be);
+    };
+    // The four slabs of one axis (normal stride ST) at o.  In FP64 at n = 8 a
+    // lane takes two neighbouring pencils of one face (lanes 0-31 the lower,
+    // 32-63 the upper face) with 16-byte loads, which the vector cache serves
+    // at twice the rate of 8-byte ones, and a half-wave swap brings both faces
+    // of a pencil together.
+    constexpr bool kPairs = N == 8 && sizeof(T) == 8 && VP;
+    auto axis = [&](auto STc, T* o, bool lo, bool hi, int64_t d) {
+        constexpr int ST = decltype(STc)::value;
+        T al, bl, ah, bh;
+        int ra = pa, rb = pb;
+        if constexpr (kPairs) {
+            const bool up = lane >= 32;
+            const int p = lane & 31, ca = p / (N / 2), cb = 2 * (p % (N / 2));
+            const bool interior = up ? hi : lo, rev = up != interior;
+            const int q0 = (ST == N * N ? ca * N + cb : ca * N * N + cb) + (rev ? (N - 1) * ST : 0);
+            const int step = rev ? -ST : ST;
+            const T* w = ub + block_base(interior ? c + (up ? d : -d) : c, 0, N3) + q0;
+            typedef T Vec __attribute__((ext_vector_type(2)));
+            Vec v[LV];
 #pragma unroll
-                    for (int kk = 0; kk < N; ++kk) {
-                        const T in = UP ? fma(T(-0.5), F.g0[kk], kk == 0 ? -F.sigma : T(0))
-                                        : fma(T(0.5), F.g1[kk], kk == N - 1 ? -F.sigma : T(0));
-                        const T bd = UP ? T(-0.5) * F.g1[kk] : T(0.5) * F.g0[kk];
-                        wgt = kk == k ? s * (interior ? in : bd) : wgt;
-                    }
-                    al = fma(wgt, wk, al);
-                    be = fma(t == 0 ? cb0 : cbn, wk, be);
-                }
-            } else {
-                T wv[N];
-                if constexpr (D == 2)
-                    pencil_load<N, VP>(wv, w + (static_cast<int64_t>(fq<N, D>(0, pa, pb)) << lb), lb);
-#pragma unroll
-                for (int k = 0; k < N; ++k) {
-                    const T in = UP ? fma(T(-0.5), F.g0[k], k == 0 ? -F.sigma : T(0))
-                                    : fma(T(0.5), F.g1[k], k == N - 1 ? -F.sigma : T(0));
-                    const T bd = UP ? T(-0.5) * F.g1[k] : T(0.5) * F.g0[k];
-                    const T wk = D == 2 ? wv[k] : ldc<T>(w + (static_cast<int64_t>(fq<N, D>(k, pa, pb)) << lb));
-                    al = fma(s * (interior ? in : bd), wk, al);
-                    if (k == 0) be = cb0 * wk;
-                    if (k == N - 1) be = fma(cbn, wk, be);
+            for (int t = 0; t < LV; ++t) {
+                v[t] = *reinterpret_cast<const Vec*>(w + t * step);
+                if (HERM) {
+                    const T s = sg(ca) * (rev ? sg(N - 1 - t) : sg(t));
+                    v[t].x *= s * sg(cb), v[t].y *= s * sg(cb + 1);
                 }
             }
-            fs[(2 * f) * N * N + pa * N + pb] = al;
-            fs[(2 * f + 1) * N * N + pa * N + pb] = be;
+            Vec va;
+            auto weigh = [&](auto cf) {
+                va = cf(0) * v[0];
+#pragma unroll
+                for (int t = 1; t < LV; ++t) va = Vec{fma(cf(t), v[t].x, va.x), fma(cf(t), v[t].y, va.y)};
+            };
+            // (uniform branches: scalar weights where both faces have the same)
+            if (lo && hi) weigh([&](int t) { return F.c[1][t]; });
+            else weigh([&](int t) { return interior ? F.c[1][t] : F.c[0][t]; });
+            const Vec vb = rev ? -v[0] : v[0];
+            half_swap(va.x, va.y, al, ah);
+            half_swap(vb.x, vb.y, bl, bh);
+            ra = ca, rb = cb + (up ? 1 : 0);
+        } else {
+            face(STc, std::integral_constant<bool, false>{}, lo, -d, al, bl);
+            face(STc, std::integral_constant<bool, true>{}, hi, d, ah, bh);
         }
+        const FacePair<T> f(al, bl, ah, bh);
+        o += ra * FR + rb;
+        o[0] = f.ap, o[FS] = f.am, o[2 * FS] = f.bd, o[3 * FS] = f.bs;
     };
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using BF = std::integral_constant<bool, false>;
-    using BT = std::integral_constant<bool, true>;
-    face(I0{}, BF{}, cx > 0, -syz, sx);
-    face(I0{}, BT{}, cx + 1 < static_cast<uint32_t>(G.mx), syz, sx);
-    face(I1{}, BF{}, cy > 0, -static_cast<int64_t>(G.mz), sy);
-    face(I1{}, BT{}, cy + 1 < static_cast<uint32_t>(G.my), G.mz, sy);
-    face(I2{}, BF{}, cz > 0, -1, sz);
-    face(I2{}, BT{}, cz + 1 < static_cast<uint32_t>(G.mz), 1, sz);
+    const bool xl = cx > 0, xh = cx + 1 < static_cast<uint32_t>(G.mx);
+    const bool yl = cy > 0, yh = cy + 1 < static_cast<uint32_t>(G.my);
+    const bool zl = cz > 0, zh = cz + 1 < static_cast<uint32_t>(G.mz);
+    T x[N], zal = T(0), zbl = T(0), zah = T(0), zbh = T(0);
+    if (pc.act) {
+        const int64_t zp = static_cast<int64_t>((pa * N + pb) * N) << lb;
+        pencil_load<N, VP>(x, ub + block_base(c, lb, N3) + zp, lb);
+        T wl[N], wh[N];
+        pencil_load<N, VP>(wl, ub + block_base(zl ? c - 1 : c, lb, N3) + zp, lb);
+        pencil_load<N, VP>(wh, ub + block_base(zh ? c + 1 : c, lb, N3) + zp, lb);
+        axis(std::integral_constant<int, N>{}, fs, yl, yh, static_cast<int64_t>(G.mz));
+        axis(std::integral_constant<int, N * N>{}, fs + 4 * FS, xl, xh, syz);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if (HERM) x[k] *= sab * sg(k), wl[k] *= sab * sg(k), wh[k] *= sab * sg(k);
+        }
+        // z faces, layers counted from the face (lower: reversed when interior)
+        T rl[N], rh[N];
+#pragma unroll
+        for (int t = 0; t < N; ++t) rl[t] = wl[N - 1 - t], rh[t] = wh[N - 1 - t];
+        if constexpr (N == 8) {   // uniform branches; n = 5 and 6 are 4% faster with selects
+            if (zl) reduce(rl, true, true, zal, zbl);
+            else reduce(wl, false, false, zal, zbl);
+            if (zh) reduce(wh, true, false, zah, zbh);
+            else reduce(rh, false, true, zah, zbh);
+        } else {
+#pragma unroll
+            for (int t = 0; t < N; ++t) rl[t] = zl ? rl[t] : wl[t], rh[t] = zh ? wh[t] : rh[t];
+            reduce(rl, zl, zl, zal, zbl);
+            reduce(rh, zh, !zh, zah, zbh);
+        }
+    }
     wave_sync();
-    // --- tangential mass of the twelve slabs: rows (second index), then columns
-    constexpr int HC = S::HC, H = S::H;
-    auto mass_pencil = [&](const T (&xin)[N], T (&out)[N]) {
-        T e[HC], o[H], E[HC], O[H];
+    auto mass_pencil = [&](T* p, int st) {
+        T xin[N], e[HC], o[H], E[HC], O[H];
+#pragma unroll
+        for (int b = 0; b < N; ++b) xin[b] = p[b * st];
         eo_split<N>(xin, e, o);
         eo_mul<N>(ME, MO, e, o, E, O);
-        eo_join<N>(E, O, out);
+        eo_join<N>(E, O, xin);
+#pragma unroll
+        for (int b = 0; b < N; ++b) p[b * st] = xin[b];
     };
-    for (int task = threadIdx.x; task < 12 * N; task += 64) {
-        const int sl = task / N, a = task - (task / N) * N;
-        T xin[N], out[N];
+    // M_z on the rows of all eight slabs, M_y on the columns of the x slabs
+    if (lane < 8 * N) mass_pencil(fs + (lane / N) * FS + (lane % N) * FR, 1);
+    wave_sync();
+    if (lane < 4 * N) mass_pencil(fs + (4 + lane / N) * FS + lane % N, FR);
+    wave_sync();
+    const FacePair<T> fy(fs + pa * FR + pb, FS), fx(fs + 4 * FS + pa * FR + pb, FS);
+    wave_sync();
+    T* A1 = L.t;
+    T* A2 = L.s;
+    if (pc.act) {  // z: lane (i, j); t = M u, w = B_z u
+        T e[HC], o[H], E[HC], O[H], r[N];
+        eo_split<N>(x, e, o);
+        eo_mul<N>(ME, MO, e, o, E, O);
+        eo_join<N>(E, O, r);
 #pragma unroll
-        for (int b = 0; b < N; ++b) xin[b] = fs[sl * N * N + a * N + b];
-        mass_pencil(xin, out);
+        for (int k = 0; k < N; ++k) A1[SL::at(pa, pb, k)] = r[k];
+        eo_mul<N>(PE, PO, e, o, E, O);
+        FacePair<T>(zal, zbl, zah, zbh).template add<N>(F, T(1), E, O);
+        eo_join<N>(E, O, r);
 #pragma unroll
-        for (int b = 0; b < N; ++b) fs[sl * N * N + a * N + b] = out[b];
+        for (int k = 0; k < N; ++k) A2[SL::at(pa, pb, k)] = r[k];
     }
     wave_sync();
-    for (int task = threadIdx.x; task < 12 * N; task += 64) {
-        const int sl = task / N, b = task - (task / N) * N;
-        T xin[N], out[N];
+    if (pc.act) {  // y: lane (i, k); a = s_x M t, b = s_y B_y t + s_z M w
+        T et[HC], ot[H], ew[HC], ow[H], E[HC], O[H], E2[HC], O2[H], r[N];
 #pragma unroll
-        for (int a = 0; a < N; ++a) xin[a] = fs[sl * N * N + a * N + b];
-        mass_pencil(xin, out);
+        for (int j = 0; j < N; ++j) r[j] = A1[SL::at(pa, j, pb)];
+        eo_split<N>(r, et, ot);
 #pragma unroll
-        for (int a = 0; a < N; ++a) fs[sl * N * N + a * N + b] = out[a];
+        for (int j = 0; j < N; ++j) r[j] = A2[SL::at(pa, j, pb)];
+        eo_split<N>(r, ew, ow);
+        eo_mul<N>(ME, MO, et, ot, E, O);
+        eo_join<N>(E, O, r);
+#pragma unroll
+        for (int j = 0; j < N; ++j) A1[SL::at(pa, j, pb)] = r[j] * sx;
+        eo_mul<N>(PE, PO, et, ot, E, O);
+        fy.template add<N>(F, T(1), E, O);
+        eo_mul<N>(ME, MO, ew, ow, E2, O2);
+#pragma unroll
+        for (int i = 0; i < HC; ++i) E[i] = fma(sy, E[i], sz * E2[i]);
+#pragma unroll
+        for (int i = 0; i < H; ++i) O[i] = fma(sy, O[i], sz * O2[i]);
+        eo_join<N>(E, O, r);
+#pragma unroll
+        for (int j = 0; j < N; ++j) A2[SL::at(pa, j, pb)] = r[j];
     }
     wave_sync();
-    // --- the lane's x-pencil of the volume product plus the face terms
-    if (pc.act) {
-        const int j = pa, k = pb;
-        T g0j = T(0), g1j = T(0), g0k = T(0), g1k = T(0);
+    if (pc.act) {  // x: lane (j, k); v = P a + M b and the x faces
+        T ea[HC], oa[H], eb[HC], ob[H], E[HC], O[H], E2[HC], O2[H], r[N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            g0j = j == i ? F.g0[i] : g0j;
-            g1j = j == i ? F.g1[i] : g1j;
-            g0k = k == i ? F.g0[i] : g0k;
-            g1k = k == i ? F.g1[i] : g1k;
+        for (int i = 0; i < N; ++i) r[i] = A1[SL::at(i, pa, pb)];
+        eo_split<N>(r, ea, oa);
+#pragma unroll
+        for (int i = 0; i < N; ++i) r[i] = A2[SL::at(i, pa, pb)];
+        eo_split<N>(r, eb, ob);
+        eo_mul<N>(PE, PO, ea, oa, E, O);
+        fx.template add<N>(F, sx, E, O);
+        eo_mul<N>(ME, MO, eb, ob, E2, O2);
+#pragma unroll
+        for (int i = 0; i < HC; ++i) E[i] += E2[i];
+#pragma unroll
+        for (int i = 0; i < H; ++i) O[i] += O2[i];
+        eo_join<N>(E, O, y);
+        if (HERM) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) y[i] *= sab * sg(i);
         }
-        const T ej0 = j == 0 ? T(1) : T(0), ejn = j == N - 1 ? T(1) : T(0);
-        const T ek0 = k == 0 ? T(1) : T(0), ekn = k == N - 1 ? T(1) : T(0);
-        const T ax0 = fs[0 * N * N + j * N + k], bx0 = fs[1 * N * N + j * N + k];
-        const T ax1 = fs[2 * N * N + j * N + k], bx1 = fs[3 * N * N + j * N + k];
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            T v = L.s[SL::at(i, j, k)];
-            v = fma(F.g0[i], bx0, fma(F.g1[i], bx1, v));                       // x faces, beta
-            if (i == 0) v += ax0;                                               // x faces, alpha
-            if (i == N - 1) v += ax1;
-            v = fma(ej0, fs[4 * N * N + i * N + k], v);                             // y faces
-            v = fma(g0j, fs[5 * N * N + i * N + k], v);
-            v = fma(ejn, fs[6 * N * N + i * N + k], v);
-            v = fma(g1j, fs[7 * N * N + i * N + k], v);
-            v = fma(ek0, fs[8 * N * N + i * N + j], v);                             // z faces
-            v = fma(g0k, fs[9 * N * N + i * N + j], v);
-            v = fma(ekn, fs[10 * N * N + i * N + j], v);
-            v = fma(g1k, fs[11 * N * N + i * N + j], v);
-            y[i] = HERM ? sab * sg(i) * v : v;
-        }
     }
     wave_sync();
+}
+
+// The face tables of a plan's wave rows.
+template <int N, typename T>
+WaveFace<N, T> wave_face(const Plan& plan) {
+    const RefData& ref = plan.ref[N];
+    const bool herm = plan.basis == TP_BASIS_HERMITE;
+    double h[N];
+    for (int k = 0; k < N; ++k) h[k] = 0.5 * ref.g0[k] * (herm ? hermite_sign(N, k) : 1.0);
+    WaveFace<N, T> F;
+    for (int k = 0; k < N; ++k) {
+        F.c[1][k] = static_cast<T>(-h[k] - (k == 0 ? plan.penalty_C * (N - 1) * N : 0.0));
+        F.c[0][k] = static_cast<T>(h[k]);
+    }
+    for (int i = 0; i < EOShape<N>::H; ++i) {
+        F.he[i] = static_cast<T>(0.5 * (h[i] + h[N - 1 - i]));
+        F.ho[i] = static_cast<T>(0.5 * (h[i] - h[N - 1 - i]));
+    }
+    if constexpr (N % 2 == 1) F.he[N / 2] = static_cast<T>(h[N / 2]);
+    return F;
 }
 
 }  // namespace tpfdm

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(64 * N, (tile_waves<N, TC, W>())) void k_sipg_tile(
 // One cell per wave (n >= 5); HERM: the Hermite-type basis.
 template <int N, typename T, bool VP, bool HERM>
 __global__ __launch_bounds__(64, 2) void k_sipg_wave(const T* __restrict__ u, T* __restrict__ v, MeshArgs G,
-                                                  const T* __restrict__ tab, FaceRef<N, T> F) {
+                                                  const T* __restrict__ tab, WaveFace<N, T> F) {
     constexpr int TAB = 2 * (EOShape<N>::SE + EOShape<N>::SO);
     __shared__ WaveLds<N, T> L;
     // FP64: the tables are read at wave-uniform global addresses (scalar
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(64, 2) void k_sipg_wave(const T* __restrict__ u, T*
     } else {
         load_table<T, TAB>(TB, tab, nullptr);   // FP32: straight from the global table
     }
-    const int64_t c = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t c = wave_tile(blockIdx.x, gridDim.x, G);
     T y[N];
     wave_sipg_cell<N, T, VP, HERM>(u, G, tb, F, c, L, y);
     const Pencil<N> pc(1);
@@ -84,9 +84,7 @@ tp_status sipg_tile_n(const Plan& plan, const MeshArgs& G, bool face_only, const
 
 template <int N, typename T>
 tp_status sipg_wave_n(const Plan& plan, const MeshArgs& G, bool face_only, const void* u, void* v, hipStream_t s) {
-    Pair<N, T> R;
-    FaceRef<N, T> F;
-    sipg_tables<N, T>(plan, face_only, R, F);
+    const WaveFace<N, T> F = wave_face<N, T>(plan);
     const T* tab = reinterpret_cast<const T*>(eo_table(plan, N, face_only ? EO_APPLY_F : EO_APPLY_A,
                                                        sizeof(T) == 8 ? 0 : 1));
     const unsigned grid = static_cast<unsigned>(G.ncells);
@@ -96,7 +94,6 @@ tp_status sipg_wave_n(const Plan& plan, const MeshArgs& G, bool face_only, const
     const bool vp = G.logB == 0 && (reinterpret_cast<uintptr_t>(ui + G.offset) % 16 == 0) &&
                     (N * sizeof(T)) % 16 == 0;
     if (plan.basis == TP_BASIS_HERMITE) {
-        flip_face_ref<N, T>(F);
         if (vp)
             hipLaunchKernelGGL((k_sipg_wave<N, T, true, true>), dim3(grid), dim3(64), 0, s, ui, vo, G, tab, F);
         else
