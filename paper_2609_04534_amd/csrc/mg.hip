@@ -169,40 +169,85 @@ __device__ __forceinline__ void kron3_accumulate(LoadF load, const double* X, co
     }
 }
 
-// b_coarse = P^T (b_fine - t_fine), t_fine = A u_fine: one coarse cell per
-// lane, summed over its children.
+// b_coarse = P^T (b_fine - t_fine), t_fine = A u_fine: 64 coarse cells per
+// workgroup of 2 N waves, wave (w, bx) on the y-z planes i = w of the children
+// in x half bx.  The z pair of children are consecutive cells: one access of
+// two values a lane loads both.  Contractions along z and y run on the loaded
+// planes, the one along x through LDS into the x-z plane j = w, half of its
+// rows per wave.  (One coarse cell a lane, all eight children in turn, took 87
+// us on 32^3 coarse cells at n = 4 and 21-25 us on any smaller level.)
 template <int N, typename TS>
-__global__ __launch_bounds__(64, 2) void k_mg_restrict(const TS* __restrict__ bf, const TS* __restrict__ tf,
-                                                     TS* __restrict__ bc,
-                                                     MeshArgs Gf, MeshArgs Gc, ProlTab<N> PT,
-                                                     const PcgState* __restrict__ st) {
+__global__ __launch_bounds__(128 * N) void k_mg_restrict(const TS* __restrict__ bf, const TS* __restrict__ tf,
+                                                         TS* __restrict__ bc, MeshArgs Gf, MeshArgs Gc,
+                                                         ProlTab<N> PT, const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
-    constexpr int N3 = N * N * N;
-    const int64_t c = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;
-    if (c >= Gc.ncells) return;
-    const uint32_t cu = static_cast<uint32_t>(c);
-    const uint32_t cz = cu % static_cast<uint32_t>(Gc.mz);
-    const uint32_t rr = cu / static_cast<uint32_t>(Gc.mz);
-    const uint32_t cy = rr % static_cast<uint32_t>(Gc.my);
-    const uint32_t cx = rr / static_cast<uint32_t>(Gc.my);
-    double acc[N3];
+    constexpr int N2 = N * N, N3 = N * N * N;
+    __shared__ double A[2][N3][64];
+    const TileCell<1> T(Gc, blockIdx.x);
+    const int w = T.w % N, bx = T.w / N, lane = T.lane;
+    // (two values aligned to one: the caller's right-hand side may be)
+    typedef TS Vec __attribute__((ext_vector_type(2), aligned(sizeof(TS))));
+    double acc[N2];
 #pragma unroll
-    for (int e = 0; e < N3; ++e) acc[e] = 0.0;
+    for (int by = 0; by < 2; ++by) {
+        const int64_t f = (static_cast<int64_t>(2 * T.cx + bx) * Gf.my + (2 * T.cy + by)) * Gf.mz + 2 * T.cz;
+        const int64_t o = Gf.offset + block_base(f, 6, N3) + (static_cast<int64_t>(w * N2) << 6);
+        double t[N2];
 #pragma unroll
-    for (int ch = 0; ch < 8; ++ch) {
-        const int bx = ch >> 2, by = (ch >> 1) & 1, bz = ch & 1;
-        const int64_t f = (static_cast<int64_t>(2 * cx + bx) * Gf.my + (2 * cy + by)) * Gf.mz + (2 * cz + bz);
-        const int64_t fb = Gf.offset + block_base(f, 6, N3);
-        kron3_accumulate<N>(
-            [&](int q) {
-                const int64_t o = fb + (static_cast<int64_t>(q) << 6);
-                return static_cast<double>(bf[o]) - static_cast<double>(tf[o]);
-            },
-            PT.p[bx], PT.p[by], PT.p[bz], acc);
+        for (int jj = 0; jj < N; ++jj) {
+            double r[2][N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const Vec bv = *reinterpret_cast<const Vec*>(bf + o + ((jj * N + k) << 6));
+                const Vec tv = *reinterpret_cast<const Vec*>(tf + o + ((jj * N + k) << 6));
+#pragma unroll
+                for (int bz = 0; bz < 2; ++bz) r[bz][k] = static_cast<double>(bv[bz]) - static_cast<double>(tv[bz]);
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                double s = 0.0;
+#pragma unroll
+                for (int bz = 0; bz < 2; ++bz)
+#pragma unroll
+                    for (int kk = 0; kk < N; ++kk) s = fma(PT.p[bz][k * N + kk], r[bz][kk], s);
+                t[jj * N + k] = s;
+            }
+        }
+#pragma unroll
+        for (int jj = 0; jj < N; ++jj)
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                double s = by == 0 ? 0.0 : acc[jj * N + k];
+#pragma unroll
+                for (int l = 0; l < N; ++l) s = fma(PT.p[by][jj * N + l], t[l * N + k], s);
+                acc[jj * N + k] = s;
+            }
     }
-    const int64_t base = Gc.offset + block_base(c, 6, N3);
 #pragma unroll
-    for (int e = 0; e < N3; ++e) bc[base + (static_cast<int64_t>(e) << 6)] = static_cast<TS>(acc[e]);
+    for (int q = 0; q < N2; ++q) A[bx][w * N2 + q][lane] = acc[q];
+    tile_sync();
+    if (!T.valid) return;
+    TS* o = bc + Gc.offset + block_base(T.c, 6, N3);
+    constexpr int NH = (N + 1) / 2;   // rows of the first wave of a plane
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        double v[2][N];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int l = 0; l < N; ++l) v[b][l] = A[b][(l * N + w) * N + k][lane];
+#pragma unroll
+        for (int ii = 0; ii < NH; ++ii) {
+            const int i = bx * NH + ii;
+            if (i >= N) break;
+            double s = 0.0;
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int l = 0; l < N; ++l) s = fma(PT.p[b][i * N + l], v[b][l], s);
+            o[((i * N + w) * N + k) << 6] = static_cast<TS>(s);
+        }
+    }
 }
 
 // u_out = u_fine + P u_coarse: one fine cell per lane, the child's embedding
@@ -242,24 +287,28 @@ __global__ __launch_bounds__(64, 2) void k_mg_prolong(const TS* __restrict__ uc,
     }
 }
 
-// u = A0^{-1} b on the coarsest level: b gathered into LDS in canonical
-// order, one row of the (column-major) inverse per thread.
+// u = A0^{-1} b on the coarsest level: one row of the (symmetric) inverse per
+// wave, its dot product with b spread over the lanes.  (One row per thread, a
+// chain of n0 dependent loads, took 28 us at n0 = 216.)
+constexpr int kCoarseRows = 4;   // rows (waves) per workgroup
 template <int N, typename TS>
-__global__ __launch_bounds__(256) void k_mg_coarse(const double* __restrict__ inv, const TS* __restrict__ b,
-                                                   TS* __restrict__ u, int64_t n0, int64_t offset, int lb,
-                                                   const PcgState* __restrict__ st) {
+__global__ __launch_bounds__(64 * kCoarseRows) void k_mg_coarse(const double* __restrict__ inv,
+                                                                const TS* __restrict__ b, TS* __restrict__ u, int n0,
+                                                                int64_t offset, int lb,
+                                                                const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
     constexpr int N3 = N * N * N;
-    __shared__ double sb[kMaxCoarse];
-    for (int64_t e = threadIdx.x; e < n0; e += 256)
-        sb[e] = static_cast<double>(b[offset + block_base(e / N3, lb, N3) + ((e % N3) << lb)]);
-    __syncthreads();
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n0) return;
+    const int row = blockIdx.x * kCoarseRows + threadIdx.y;
+    if (row >= n0) return;
+    auto pos = [&](int e) { return offset + block_base(e / N3, lb, N3) + (static_cast<int64_t>(e % N3) << lb); };
+    const double* a = inv + static_cast<int64_t>(row) * n0;
     double s = 0.0;
-    for (int64_t j = 0; j < n0; ++j) s = fma(inv[j * n0 + i], sb[j], s);
-    u[offset + block_base(i / N3, lb, N3) + ((i % N3) << lb)] = static_cast<TS>(s);
+#pragma unroll 4
+    for (int j = threadIdx.x; j < n0; j += 64) s = fma(a[j], static_cast<double>(b[pos(j)]), s);
+    s = wave_sum(s);
+    if (threadIdx.x == 0) u[pos(row)] = static_cast<TS>(s);
 }
+inline unsigned coarse_grid(int64_t n0) { return static_cast<unsigned>((n0 + kCoarseRows - 1) / kCoarseRows); }
 
 // Partial (a, b) per 64-cell tile (the layout of the PCG partials).
 template <int N, typename TS>
@@ -487,18 +536,20 @@ __device__ __forceinline__ void wave_kron3(const Pencil<N>& pc, double* slab, co
     wave_sync();
 }
 
-// b_coarse = P^T (b_fine - t_fine), one coarse cell per wave, summed over
-// its eight children.
+// b_coarse = P^T (b_fine - t_fine), one coarse cell per workgroup of eight
+// waves, one child per wave; the children's contributions are summed in LDS in
+// a fixed order.  (The eight children in turn by one wave took 15 us on the
+// smallest levels.)
 template <int N, bool VP, typename TS = double>
-__global__ __launch_bounds__(64, 2) void k_mg_restrict_wave(const TS* __restrict__ bf,
-                                                          const TS* __restrict__ tf, TS* __restrict__ bc,
-                                                          MeshArgs Gf, MeshArgs Gc, ProlTab<N> PT,
-                                                          const PcgState* __restrict__ st) {
+__global__ __launch_bounds__(512) void k_mg_restrict_wave(const TS* __restrict__ bf, const TS* __restrict__ tf,
+                                                          TS* __restrict__ bc, MeshArgs Gf, MeshArgs Gc,
+                                                          ProlTab<N> PT, const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
-    __shared__ double slab[Slab<N>::size];
+    constexpr int N3 = N * N * N;
+    __shared__ double slab[8][Slab<N>::size];
     __shared__ double tabs[2 * N * N];
-    for (int e = threadIdx.x; e < 2 * N * N; e += 64) tabs[e] = PT.p[e / (N * N)][e % (N * N)];
-    wave_sync();
+    const int ch = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    for (int e = ch * 64 + threadIdx.x; e < 2 * N * N; e += 512) tabs[e] = PT.p[e / (N * N)][e % (N * N)];
     const int64_t c = blockIdx.x;
     const uint32_t cu = static_cast<uint32_t>(c);
     const uint32_t cz = cu % static_cast<uint32_t>(Gc.mz);
@@ -506,31 +557,30 @@ __global__ __launch_bounds__(64, 2) void k_mg_restrict_wave(const TS* __restrict
     const uint32_t cy = rr % static_cast<uint32_t>(Gc.my);
     const uint32_t cx = rr / static_cast<uint32_t>(Gc.my);
     const Pencil<N> pc(1);
-    double acc[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) acc[i] = 0.0;
-    for (int ch = 0; ch < 8; ++ch) {
-        const int bx = ch >> 2, by = (ch >> 1) & 1, bz = ch & 1;
-        const int64_t f = (static_cast<int64_t>(2 * cx + bx) * Gf.my + (2 * cy + by)) * Gf.mz + (2 * cz + bz);
-        double z[N], out[N];
-        if (pc.act) {
-            const int64_t pb = zpencil_base<N>(Gf, f, pc);
-            double tv[N];
-            pencil_load<N, VP>(z, bf + pb, Gf.logB);
-            pencil_load<N, VP>(tv, tf + pb, Gf.logB);
-#pragma unroll
-            for (int k = 0; k < N; ++k) z[k] -= tv[k];
-        }
-        wave_kron3<N>(pc, slab, tabs + bx * N * N, tabs + by * N * N, tabs + bz * N * N, z, out);
-        if (pc.act)
-#pragma unroll
-            for (int i = 0; i < N; ++i) acc[i] += out[i];
-    }
+    const int bx = ch >> 2, by = (ch >> 1) & 1, bz = ch & 1;
+    const int64_t f = (static_cast<int64_t>(2 * cx + bx) * Gf.my + (2 * cy + by)) * Gf.mz + (2 * cz + bz);
+    double z[N], out[N];
     if (pc.act) {
-        TS* cb = bc + Gc.offset + block_base(c, Gc.logB, N * N * N);
+        const int64_t pb = zpencil_base<N>(Gf, f, pc);
+        double tv[N];
+        pencil_load<N, VP>(z, bf + pb, Gf.logB);
+        pencil_load<N, VP>(tv, tf + pb, Gf.logB);
 #pragma unroll
-        for (int i = 0; i < N; ++i)
-            cb[static_cast<int64_t>((i * N + pc.pa) * N + pc.pb) << Gc.logB] = static_cast<TS>(acc[i]);
+        for (int k = 0; k < N; ++k) z[k] -= tv[k];
+    }
+    tile_sync();
+    wave_kron3<N>(pc, slab[ch], tabs + bx * N * N, tabs + by * N * N, tabs + bz * N * N, z, out);
+    if (pc.act) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) slab[ch][(i * N + pc.pa) * N + pc.pb] = out[i];
+    }
+    tile_sync();
+    TS* cb = bc + Gc.offset + block_base(c, Gc.logB, N3);
+    for (int q = ch * 64 + threadIdx.x; q < N3; q += 512) {
+        double s = slab[0][q];
+#pragma unroll
+        for (int k = 1; k < 8; ++k) s += slab[k][q];
+        cb[static_cast<int64_t>(q) << Gc.logB] = static_cast<TS>(s);
     }
 }
 
@@ -598,27 +648,38 @@ struct DegTab {
     double e[N][2];
 };
 
-// bc = E^T (b - t), one thread per coarse unknown (cell, jx, jy, jz).
+// bc = E^T (b - t), one cell per wave: lane (a, q) sums its z-pencil against
+// both coarse z functions, the eight coarse unknowns are wave sums.
 template <int N, typename TS = double>
 __global__ __launch_bounds__(64) void k_mg_deg_restrict(const TS* __restrict__ b, const TS* __restrict__ t,
                                                         double* __restrict__ bc, MeshArgs G, DegTab<N> E,
                                                         const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;
-    if (idx >= G.ncells * 8) return;
-    const int64_t c = idx >> 3;
-    const int jx = static_cast<int>(idx >> 2) & 1, jy = static_cast<int>(idx >> 1) & 1, jz = static_cast<int>(idx) & 1;
-    const int64_t base = G.offset + block_base(c, G.logB, N * N * N);
-    double s = 0.0;
-    for (int a = 0; a < N; ++a)
-        for (int q = 0; q < N; ++q) {
-            const double wab = E.e[a][jx] * E.e[q][jy];
-            for (int k = 0; k < N; ++k) {
-                const int64_t o = base + (static_cast<int64_t>((a * N + q) * N + k) << G.logB);
-                s = fma(wab * E.e[k][jz], static_cast<double>(b[o]) - static_cast<double>(t[o]), s);
-            }
+    const int64_t c = blockIdx.x;
+    const Pencil<N> pc(1);
+    double s0 = 0.0, s1 = 0.0, ex[2] = {0.0, 0.0}, ey[2] = {0.0, 0.0};
+    if (pc.act) {
+        const int64_t pb = zpencil_base<N>(G, c, pc);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int64_t o = pb + (static_cast<int64_t>(k) << G.logB);
+            const double v = static_cast<double>(b[o]) - static_cast<double>(t[o]);
+            s0 = fma(E.e[k][0], v, s0);
+            s1 = fma(E.e[k][1], v, s1);
         }
-    bc[idx] = s;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                ex[j] = pc.pa == i ? E.e[i][j] : ex[j];
+                ey[j] = pc.pb == i ? E.e[i][j] : ey[j];
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const double v = wave_sum(ex[j >> 2] * ey[(j >> 1) & 1] * ((j & 1) ? s1 : s0));
+        if (threadIdx.x == 0) bc[c * 8 + j] = v;
+    }
 }
 
 // uout = u + E uc, one thread per fine unknown.
@@ -757,9 +818,8 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
     TS* Lt = static_cast<TS*>(L.t);
     const unsigned grid = static_cast<unsigned>((L.G.ncells + 63) / 64);
     if (l + 1 == m->lv.size()) {
-        const unsigned cg = static_cast<unsigned>((m->n0 + 255) / 256);
-        hipLaunchKernelGGL((k_mg_coarse<N, TS>), dim3(cg), dim3(256), 0, s, m->coarse_inv, b, u, m->n0, L.G.offset,
-                           L.G.logB, st);
+        hipLaunchKernelGGL((k_mg_coarse<N, TS>), dim3(coarse_grid(m->n0)), dim3(64, kCoarseRows), 0, s, m->coarse_inv,
+                           b, u, static_cast<int>(m->n0), L.G.offset, L.G.logB, st);
         return check_launch("coarse solve");
     }
     const TileTab<N, MgTC<TS>, HERM> R = tile_tab<N, MgTC<TS>, HERM>(plan, false);
@@ -800,8 +860,8 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
     }
     if (!wide)
         hipLaunchKernelGGL((k_mg_apply<N, HERM, TS>), dim3(grid), dim3(64, N), 0, s, u, Lt, L.G, R, st);
-    hipLaunchKernelGGL((k_mg_restrict<N, TS>), dim3(static_cast<unsigned>((C.G.ncells + 63) / 64)), dim3(64), 0, s, b,
-                       Lt, Cb, L.G, C.G, PT, st);
+    hipLaunchKernelGGL((k_mg_restrict<N, TS>), dim3(tile_grid(C.G, 1)), dim3(64, 2 * N), 0, s, b, Lt, Cb, L.G, C.G,
+                       PT, st);
     tp_status stt = check_launch("level transfer");
     if (stt != TP_OK) return stt;
     stt = vcycle_level<N, TI, HERM, TS>(m, l + 1, Cb, Cu, st, s);
@@ -825,9 +885,8 @@ tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const 
     const unsigned grid = static_cast<unsigned>(L.G.ncells);
     const bool last = l + 1 == m->lv.size();
     if (last && !m->deg) {
-        const unsigned cg = static_cast<unsigned>((m->n0 + 255) / 256);
-        hipLaunchKernelGGL((k_mg_coarse<N, TS>), dim3(cg), dim3(256), 0, s, m->coarse_inv, b, u, m->n0,
-                           L.G.offset, L.G.logB, st);
+        hipLaunchKernelGGL((k_mg_coarse<N, TS>), dim3(coarse_grid(m->n0)), dim3(64, kCoarseRows), 0, s, m->coarse_inv,
+                           b, u, static_cast<int>(m->n0), L.G.offset, L.G.logB, st);
         return check_launch("coarse solve");
     }
     const WaveFace<N, TS> F = wave_face<N, TS>(plan);
@@ -851,10 +910,9 @@ tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const 
         // solve, u + E u_c
         const DegTab<N> E = deg_table<N>();
         hipLaunchKernelGGL((k_mg_apply_wave<N, VP, TS>), dim3(grid), dim3(64), 0, s, u, Lt, L.G, tabA, F, st);
-        hipLaunchKernelGGL((k_mg_deg_restrict<N, TS>), dim3(static_cast<unsigned>((m->n0 + 63) / 64)), dim3(64), 0, s,
-                           b, Lt, m->deg_b, L.G, E, st);
-        hipLaunchKernelGGL((k_mg_coarse<2, double>), dim3(static_cast<unsigned>((m->n0 + 255) / 256)), dim3(256), 0, s,
-                           m->coarse_inv, m->deg_b, m->deg_u, m->n0, int64_t(0), 0, st);
+        hipLaunchKernelGGL((k_mg_deg_restrict<N, TS>), dim3(grid), dim3(64), 0, s, b, Lt, m->deg_b, L.G, E, st);
+        hipLaunchKernelGGL((k_mg_coarse<2, double>), dim3(coarse_grid(m->n0)), dim3(64, kCoarseRows), 0, s,
+                           m->coarse_inv, m->deg_b, m->deg_u, static_cast<int>(m->n0), int64_t(0), 0, st);
         hipLaunchKernelGGL((k_mg_deg_prolong<N, TS>),
                            dim3(static_cast<unsigned>((L.G.ncells * N * N * N + 63) / 64)), dim3(64), 0, s, m->deg_u,
                            u, Lt, L.G, E, st);
@@ -869,7 +927,7 @@ tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const 
     TS* Cb = static_cast<TS*>(C.b);
     TS* Cu = static_cast<TS*>(C.u);
     hipLaunchKernelGGL((k_mg_apply_wave<N, VP, TS>), dim3(grid), dim3(64), 0, s, u, Lt, L.G, tabA, F, st);
-    hipLaunchKernelGGL((k_mg_restrict_wave<N, VP, TS>), dim3(static_cast<unsigned>(C.G.ncells)), dim3(64), 0, s, b,
+    hipLaunchKernelGGL((k_mg_restrict_wave<N, VP, TS>), dim3(static_cast<unsigned>(C.G.ncells)), dim3(64, 8), 0, s, b,
                        Lt, Cb, L.G, C.G, PT, st);
     tp_status stt = check_launch("level transfer");
     if (stt != TP_OK) return stt;
@@ -997,7 +1055,6 @@ tp_status coarse_probe_deg(const tp_mg* m, std::vector<double>& A) {
     if (st == TP_OK) st = launch_fill(pu, L.elems, TP_F64, 0, true, nullptr);
     const PcgState* none = nullptr;
     const unsigned gf = static_cast<unsigned>((L.G.ncells * N * N * N + 63) / 64);
-    const unsigned gc = static_cast<unsigned>((n0 + 63) / 64);
     for (int64_t j = 0; st == TP_OK && j < n0; ++j) {
         st = launch_fill(ec, n0, TP_F64, 0, true, nullptr);
         if (st != TP_OK) break;
@@ -1010,7 +1067,8 @@ tp_status coarse_probe_deg(const tp_mg* m, std::vector<double>& A) {
         hipLaunchKernelGGL((k_mg_deg_prolong<N>), dim3(gf), dim3(64), 0, nullptr, ec, zf, pu, L.G, E, none);
         hipLaunchKernelGGL((k_mg_apply_wave<N, false>), dim3(static_cast<unsigned>(L.G.ncells)), dim3(64), 0, nullptr,
                            pu, pt, L.G, tabA, F, none);
-        hipLaunchKernelGGL((k_mg_deg_restrict<N>), dim3(gc), dim3(64), 0, nullptr, pt, zf, cc, L.G, E, none);
+        hipLaunchKernelGGL((k_mg_deg_restrict<N>), dim3(static_cast<unsigned>(L.G.ncells)), dim3(64), 0, nullptr, pt, zf,
+                           cc, L.G, E, none);
         st = check_launch("degree-level probe");
         if (st != TP_OK) break;
         e = hipMemcpy(col.data(), cc, cb, hipMemcpyDeviceToHost);

@@ -62,31 +62,43 @@ __global__ __launch_bounds__(64 * N, (tile_waves<N, double, W>())) void k_pcg_aq
     if (threadIdx.x == 0 && threadIdx.y == 0) part[blockIdx.x] = dot;
 }
 
-// Fixed-order sum of count partials by one 256-thread workgroup.
-__device__ __forceinline__ double block_sum(const double* __restrict__ part, int64_t count, double* red) {
-    double s = 0.0;
-    for (int64_t i = threadIdx.x; i < count; i += 256) s += part[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (static_cast<int>(threadIdx.x) < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+// Fixed-order sums of K arrays of count partials (array k starts at part +
+// k count) by one workgroup of kRed threads, returned to every thread.  (By
+// 256 threads, one array after the other, 13824 partials took 15 us an array.)
+constexpr int kRed = 1024;
+template <int K>
+__device__ __forceinline__ void block_sums(const double* __restrict__ part, int64_t count, double (&out)[K]) {
+    __shared__ double red[K][kRed / 64];
+    double s[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[k] = 0.0;
+#pragma unroll 4
+    for (int64_t i = threadIdx.x; i < count; i += kRed)
+#pragma unroll
+        for (int k = 0; k < K; ++k) s[k] += part[k * count + i];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        s[k] = wave_sum(s[k]);
+        if (threadIdx.x % 64 == 0) red[k][threadIdx.x / 64] = s[k];
     }
-    const double r = red[0];
     __syncthreads();
-    return r;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        out[k] = red[k][0];
+#pragma unroll
+        for (int w = 1; w < kRed / 64; ++w) out[k] += red[k][w];
+    }
 }
 
 // 0.  After the start kernel: (r, z), (r, r), (b, b) -> state.  norm 0:
 // converged when (r, r) <= rtol^2 (b, b); norm 1: when (r, z) <= rtol^2
 // (r_0, z_0), the preconditioned residual norm reduced by rtol.
-__global__ __launch_bounds__(256) void k_pcg_reduce_start(const double* __restrict__ part, int64_t count,
-                                                          PcgState* __restrict__ st, double rtol, int maxit,
-                                                          int norm) {
-    __shared__ double red[256];
-    const double rz = block_sum(part, count, red);
-    const double rr = block_sum(part + count, count, red);
-    const double bb = block_sum(part + 2 * count, count, red);
+__global__ __launch_bounds__(kRed) void k_pcg_reduce_start(const double* __restrict__ part, int64_t count,
+                                                           PcgState* __restrict__ st, double rtol, int maxit,
+                                                           int norm) {
+    double v[3];
+    block_sums<3>(part, count, v);
+    const double rz = v[0], rr = v[1], bb = v[2];
     if (threadIdx.x == 0) {
         PcgState s;
         s.rz = rz;
@@ -105,28 +117,28 @@ __global__ __launch_bounds__(256) void k_pcg_reduce_start(const double* __restri
 }
 
 // 2.  alpha = (r, z) / (p, q).
-__global__ __launch_bounds__(256) void k_pcg_reduce_alpha(const double* __restrict__ part, int64_t count,
-                                                          PcgState* __restrict__ st) {
+__global__ __launch_bounds__(kRed) void k_pcg_reduce_alpha(const double* __restrict__ part, int64_t count,
+                                                           PcgState* __restrict__ st) {
     if (st->done) return;
-    __shared__ double red[256];
-    const double pq = block_sum(part, count, red);
+    double pq[1];
+    block_sums<1>(part, count, pq);
     if (threadIdx.x == 0) {
-        st->pq = pq;
-        if (!(pq > 0.0) || !finite(pq)) {
+        st->pq = pq[0];
+        if (!(pq[0] > 0.0) || !finite(pq[0])) {
             st->done = 2;
         } else {
-            st->alpha = st->rz / pq;
+            st->alpha = st->rz / pq[0];
         }
     }
 }
 
 // 4.  beta, the iteration count and the convergence test.
-__global__ __launch_bounds__(256) void k_pcg_reduce_beta(const double* __restrict__ part, int64_t count,
-                                                         PcgState* __restrict__ st) {
+__global__ __launch_bounds__(kRed) void k_pcg_reduce_beta(const double* __restrict__ part, int64_t count,
+                                                          PcgState* __restrict__ st) {
     if (st->done) return;
-    __shared__ double red[256];
-    const double rz = block_sum(part, count, red);
-    const double rr = block_sum(part + count, count, red);
+    double v[2];
+    block_sums<2>(part, count, v);
+    const double rz = v[0], rr = v[1];
     if (threadIdx.x == 0) {
         const double rz_old = st->rz;
         st->beta = rz / rz_old;
@@ -705,7 +717,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
     else
         hipLaunchKernelGGL((k_pcg_start_wave<N, TI, false>), dim3(nwg), dim3(64), 0, stream, b,
                            x_zero ? nullptr : s->q, x, s->xw, s->r, s->z, s->p, G, tabS, s->part, cnt);
-    hipLaunchKernelGGL(k_pcg_reduce_start, dim3(1), dim3(256), 0, stream, s->part, cnt, s->st, rtol, maxit,
+    hipLaunchKernelGGL(k_pcg_reduce_start, dim3(1), dim3(kRed), 0, stream, s->part, cnt, s->st, rtol, maxit,
                        s->norm);
     tp_status st = check_launch("PCG start");
     if (st != TP_OK) return st;
@@ -755,7 +767,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                 else
                     hipLaunchKernelGGL((k_pcg_aq_wave<N, false, false>), dim3(nwg), dim3(64), 0, cs, s->p, s->q, G,
                                        tabA, F, s->st, s->part);
-                hipLaunchKernelGGL(k_pcg_reduce_alpha, dim3(1), dim3(256), 0, cs, s->part, aqcnt, s->st);
+                hipLaunchKernelGGL(k_pcg_reduce_alpha, dim3(1), dim3(kRed), 0, cs, s->part, aqcnt, s->st);
                 if (s->mg) {
                     if constexpr (!kLane) {
                         if (vp)
@@ -796,7 +808,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                 else
                     hipLaunchKernelGGL((k_pcg_update_wave<N, TI, false, false>), dim3(nwg), dim3(64), 0, cs, s->xw,
                                        s->r, s->z, s->p, s->q, G, tabS, s->st, s->part, cnt);
-                hipLaunchKernelGGL(k_pcg_reduce_beta, dim3(1), dim3(256), 0, cs, s->part, cnt, s->st);
+                hipLaunchKernelGGL(k_pcg_reduce_beta, dim3(1), dim3(kRed), 0, cs, s->part, cnt, s->st);
                 if (s->mg && mg_storage(s->mg) == TP_F32)
                     hipLaunchKernelGGL(k_pcg_dir<float>, dim3(dgrid), dim3(256), 0, cs, mg_result32(s->mg), s->p,
                                        s->elems, s->st);
