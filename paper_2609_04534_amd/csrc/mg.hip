@@ -136,37 +136,57 @@ __global__ __launch_bounds__(64 * N, (tile_waves<N, MgTC<TS>, W>())) void k_mg_s
     }
 }
 
-// acc += (X (x) Y (x) Z) w for one cell, the input streamed one x-plane at
-// a time (X acts on x, the slowest index).
-template <int N, typename LoadF>
-__device__ __forceinline__ void kron3_accumulate(LoadF load, const double* X, const double* Y, const double* Z,
-                                                 double (&acc)[N * N * N]) {
+// The child's 1D embedding (or its transpose) of a lane's cell along an axis.
+template <int N>
+__device__ __forceinline__ void child_matrix(const ProlTab<N>& P, bool upper, double (&m)[N * N]) {
 #pragma unroll
-    for (int ip = 0; ip < N; ++ip) {
-        double pl[N * N];
+    for (int e = 0; e < N * N; ++e) m[e] = upper ? P.p[1][e] : P.p[0][e];
+}
+
+// v <- (X (x) Y (x) Z) v for the lane's cell, each factor the embedding P of
+// the cell's half along that axis (ux, uy, uz: upper); v the plane i = w in
+// and out, the x contraction through LDS.  A: N^3 x 64 doubles whose plane
+// i = w the wave owns on entry and on return.
+template <int N>
+__device__ __forceinline__ void tile_kron(const ProlTab<N>& P, bool ux, bool uy, bool uz, int w, int lane,
+                                          double (*A)[64], double (&v)[N * N]) {
+    constexpr int N2 = N * N;
+    auto pencil = [&](const double (&m)[N2], double (&x)[N2], int base, int st) {
+        double t[N];
 #pragma unroll
-        for (int q = 0; q < N * N; ++q) pl[q] = load(ip * N * N + q);
-        double t1[N * N];
+        for (int r = 0; r < N; ++r) {
+            t[r] = m[r * N] * x[base];
 #pragma unroll
-        for (int j = 0; j < N; ++j)
+            for (int k = 1; k < N; ++k) t[r] = fma(m[r * N + k], x[base + k * st], t[r]);
+        }
 #pragma unroll
-            for (int k = 0; k < N; ++k) {
-                double sacc = 0.0;
+        for (int r = 0; r < N; ++r) x[base + r * st] = t[r];
+    };
+    double m[N2];
+    child_matrix<N>(P, uz, m);
 #pragma unroll
-                for (int kk = 0; kk < N; ++kk) sacc = fma(Z[k * N + kk], pl[j * N + kk], sacc);
-                t1[j * N + k] = sacc;
-            }
+    for (int jj = 0; jj < N; ++jj) pencil(m, v, jj * N, 1);
+    child_matrix<N>(P, uy, m);
 #pragma unroll
-        for (int j = 0; j < N; ++j)
+    for (int k = 0; k < N; ++k) pencil(m, v, k, N);
 #pragma unroll
-            for (int k = 0; k < N; ++k) {
-                double sacc = 0.0;
+    for (int q = 0; q < N2; ++q) A[w * N2 + q][lane] = v[q];
+    tile_sync();
+    child_matrix<N>(P, ux, m);
+    double x[N2];   // x-z plane j = w
 #pragma unroll
-                for (int jj = 0; jj < N; ++jj) sacc = fma(Y[j * N + jj], t1[jj * N + k], sacc);
+    for (int l = 0; l < N; ++l)
 #pragma unroll
-                for (int i = 0; i < N; ++i) acc[(i * N + j) * N + k] = fma(X[i * N + ip], sacc, acc[(i * N + j) * N + k]);
-            }
-    }
+        for (int k = 0; k < N; ++k) x[l * N + k] = A[(l * N + w) * N + k][lane];
+#pragma unroll
+    for (int k = 0; k < N; ++k) pencil(m, x, k, N);
+#pragma unroll
+    for (int l = 0; l < N; ++l)
+#pragma unroll
+        for (int k = 0; k < N; ++k) A[(l * N + w) * N + k][lane] = x[l * N + k];
+    tile_sync();
+#pragma unroll
+    for (int q = 0; q < N2; ++q) v[q] = A[w * N2 + q][lane];
 }
 
 // b_coarse = P^T (b_fine - t_fine), t_fine = A u_fine: 64 coarse cells per
@@ -250,41 +270,28 @@ __global__ __launch_bounds__(128 * N) void k_mg_restrict(const TS* __restrict__ 
     }
 }
 
-// u_out = u_fine + P u_coarse: one fine cell per lane, the child's embedding
-// selected per lane.
+// u_out = u_fine + P u_coarse: 64 fine cells per workgroup of N waves, the
+// child's embedding selected per lane.
 template <int N, typename TS>
-__global__ __launch_bounds__(64, 2) void k_mg_prolong(const TS* __restrict__ uc, const TS* __restrict__ uf,
-                                                    TS* __restrict__ uout,
-                                                    MeshArgs Gf, MeshArgs Gc, ProlTab<N> P,
-                                                    const PcgState* __restrict__ st) {
+__global__ __launch_bounds__(64 * N, N == 4 ? 3 : 4) void k_mg_prolong(const TS* __restrict__ uc, const TS* __restrict__ uf,
+                                                          TS* __restrict__ uout, MeshArgs Gf, MeshArgs Gc,
+                                                          ProlTab<N> P, const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
-    constexpr int N3 = N * N * N, N2 = N * N;
-    const int64_t f = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;
-    if (f >= Gf.ncells) return;
-    const uint32_t fu = static_cast<uint32_t>(f);
-    const uint32_t fz = fu % static_cast<uint32_t>(Gf.mz);
-    const uint32_t rr = fu / static_cast<uint32_t>(Gf.mz);
-    const uint32_t fy = rr % static_cast<uint32_t>(Gf.my);
-    const uint32_t fx = rr / static_cast<uint32_t>(Gf.my);
-    const int64_t c = (static_cast<int64_t>(fx / 2) * Gc.my + fy / 2) * Gc.mz + fz / 2;
-    double X[N2], Y[N2], Z[N2];
+    constexpr int N2 = N * N, N3 = N * N * N;
+    __shared__ double A[N3][64];
+    const TileCell<1> T(Gf, blockIdx.x);
+    const int64_t c = (static_cast<int64_t>(T.cx / 2) * Gc.my + T.cy / 2) * Gc.mz + T.cz / 2;
+    const TS* wc = uc + Gc.offset + block_base(c, 6, N3) + (static_cast<int64_t>(T.w * N2) << 6);
+    const int64_t o = Gf.offset + block_base(T.c, 6, N3) + (static_cast<int64_t>(T.w * N2) << 6);
+    double v[N2], uv[N2];
 #pragma unroll
-    for (int e = 0; e < N2; ++e) {
-        X[e] = (fx & 1) ? P.p[1][e] : P.p[0][e];
-        Y[e] = (fy & 1) ? P.p[1][e] : P.p[0][e];
-        Z[e] = (fz & 1) ? P.p[1][e] : P.p[0][e];
-    }
-    const TS* w = uc + Gc.offset + block_base(c, 6, N3);
-    double acc[N3];
+    for (int q = 0; q < N2; ++q) v[q] = static_cast<double>(wc[q << 6]);
 #pragma unroll
-    for (int e = 0; e < N3; ++e) acc[e] = 0.0;
-    kron3_accumulate<N>([&](int q) { return static_cast<double>(w[static_cast<int64_t>(q) << 6]); }, X, Y, Z, acc);
-    const int64_t base = Gf.offset + block_base(f, 6, N3);
+    for (int q = 0; q < N2; ++q) uv[q] = static_cast<double>(uf[o + (q << 6)]);
+    tile_kron<N>(P, T.cx & 1, T.cy & 1, T.cz & 1, T.w, T.lane, A, v);
+    if (!T.valid) return;
 #pragma unroll
-    for (int e = 0; e < N3; ++e) {
-        const int64_t o = base + (static_cast<int64_t>(e) << 6);
-        uout[o] = static_cast<TS>(static_cast<double>(uf[o]) + acc[e]);
-    }
+    for (int q = 0; q < N2; ++q) uout[o + (q << 6)] = static_cast<TS>(uv[q] + v[q]);
 }
 
 // u = A0^{-1} b on the coarsest level: one row of the (symmetric) inverse per
@@ -309,6 +316,155 @@ __global__ __launch_bounds__(64 * kCoarseRows) void k_mg_coarse(const double* __
     if (threadIdx.x == 0) u[pos(row)] = static_cast<TS>(s);
 }
 inline unsigned coarse_grid(int64_t n0) { return static_cast<unsigned>((n0 + kCoarseRows - 1) / kCoarseRows); }
+
+// The V-cycle below and including a level of at most 64 cells (n <= 4) in one
+// workgroup of N waves with every level vector but the entry level's
+// right-hand side in LDS.  On such levels a launch per step is all latency:
+// 19 launches of 5-10 us each against one of 40 us for 4^3, 2^3 and one cell.
+// Levels hold at most 64, 8 and 1 cells; all vectors are [q][64 lanes], the
+// second and third level's at lane offsets of one shared block.
+constexpr int kTailLevels = 3;
+constexpr int kTailUnknowns = 256;   // of the coarsest level: its inverse is read by one CU
+template <int N, typename TI, bool HERM, typename TS>
+struct TailArgs {
+    int levels;                       // 2 or 3, the coarsest included
+    int n0;                           // unknowns of the coarsest level
+    MeshArgs G[kTailLevels];
+    TileTab<N, MgTC<TS>, HERM> R;
+    TileInv<N, TI> E[kTailLevels - 1];   // of D^{-1} (no weight)
+    ProlTab<N> P, PT;
+    double omega[3];
+    const double* inv;
+};
+template <int N, typename TI, bool HERM, typename TS>
+__global__ __launch_bounds__(64 * N, 1) void k_mg_tail(const TS* __restrict__ b0, TS* __restrict__ u0,
+                                                       TailArgs<N, TI, HERM, TS> M, const PcgState* __restrict__ st) {
+    using TC = MgTC<TS>;
+    if (done_flag(st)) return;
+    constexpr int N2 = N * N, N3 = N * N * N;
+    __shared__ TS ua[N3 * 64], ta[N3 * 64], lower[N3 * 64];
+    __shared__ double A[N3][64];
+    TC(*At)[64] = reinterpret_cast<TC(*)[64]>(&A[0][0]);
+    TI(*Ai)[64] = reinterpret_cast<TI(*)[64]>(&A[0][0]);
+    const int lane = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    // correction, scratch and right-hand side of a level
+    auto u_of = [&](int l) { return l == 0 ? ua : lower + (l == 1 ? 0 : 24); };
+    auto t_of = [&](int l) { return l == 0 ? ta : lower + 8; };
+    auto b_of = [&](int l) { return lower + (l == 1 ? 16 : 25); };
+    // own plane of the right-hand side (the entry level's is in global memory)
+    auto rhs = [&](int l, const TileCell<1>& T, int q) {
+        return l == 0 ? b0[((T.w * N2 + q) << 6) + T.c] : b_of(l)[((T.w * N2 + q) << 6) + T.c];
+    };
+    // one update u_to = u_from + omega D^{-1} (b - A u_from), or from zero
+    auto update = [&](int l, const TS* from, TS* to, double omega) {
+        const TileCell<1> T(M.G[l], 0);
+        TI v[N2];
+        Cells<TI, 1> vi[N2];
+#pragma unroll
+        for (int q = 0; q < N2; ++q) v[q] = static_cast<TI>(static_cast<TC>(rhs(l, T, q)));
+        if (from) {
+            Cells<TC, 1> out[N2];
+            tile_sipg<N, TS, TC, 1, 6, HERM>(from, M.G[l], M.R, T, reinterpret_cast<Cells<TC, 1>(*)[64]>(At), out);
+#pragma unroll
+            for (int q = 0; q < N2; ++q) v[q] = static_cast<TI>(static_cast<TC>(rhs(l, T, q)) - out[q].v[0]);
+            if constexpr (sizeof(TC) != sizeof(TI)) tile_sync();
+        }
+#pragma unroll
+        for (int q = 0; q < N2; ++q) vi[q].v[0] = v[q];
+        tile_fdm<N, TI, 1>(M.E[l], T, reinterpret_cast<Cells<TI, 1>(*)[64]>(Ai), vi);
+        if (T.valid) {
+#pragma unroll
+            for (int q = 0; q < N2; ++q) {
+                const int o = ((w * N2 + q) << 6) + lane;
+                const double uv = from ? static_cast<double>(from[o]) : 0.0;
+                to[o] = static_cast<TS>(fma(omega, static_cast<double>(vi[q].v[0]), uv));
+            }
+        }
+        tile_sync();
+    };
+    const int last = M.levels - 1;
+#pragma unroll 1
+    for (int l = 0; l < last; ++l) {
+        TS* u = u_of(l);
+        TS* t = t_of(l);
+        update(l, nullptr, u, M.omega[0]);
+#pragma unroll 1
+        for (int j = 1; j < 3; ++j) update(l, j == 1 ? u : t, j == 1 ? t : u, M.omega[j]);
+        // residual, each child's part of the restriction, sums over children
+        const TileCell<1> T(M.G[l], 0);
+        Cells<TC, 1> out[N2];
+        tile_sipg<N, TS, TC, 1, 6, HERM>(u, M.G[l], M.R, T, reinterpret_cast<Cells<TC, 1>(*)[64]>(At), out);
+        tile_sync();
+        double v[N2];
+#pragma unroll
+        for (int q = 0; q < N2; ++q)
+            v[q] = static_cast<double>(rhs(l, T, q)) - static_cast<double>(static_cast<TS>(out[q].v[0]));
+        tile_kron<N>(M.PT, T.cx & 1, T.cy & 1, T.cz & 1, w, lane, A, v);
+        tile_sync();
+        const MeshArgs& Gf = M.G[l];
+        const MeshArgs& Gc = M.G[l + 1];
+        TS* bc = b_of(l + 1);
+        const int nc = static_cast<int>(Gc.ncells);
+        for (int e = w * 64 + lane; e < N3 * nc; e += 64 * N) {
+            const int q = e / nc, c = e - q * nc;
+            const int cz = c % Gc.mz, cy = (c / Gc.mz) % Gc.my, cx = c / (Gc.mz * Gc.my);
+            double s = 0.0;
+#pragma unroll
+            for (int ch = 0; ch < 8; ++ch)
+                s += A[q][((2 * cx + (ch >> 2)) * Gf.my + 2 * cy + ((ch >> 1) & 1)) * Gf.mz + 2 * cz + (ch & 1)];
+            bc[(q << 6) + c] = static_cast<TS>(s);
+        }
+        tile_sync();
+    }
+    {   // dense solve of the coarsest level: rows over lanes, columns over waves
+        const TS* b = b_of(last);
+        TS* u = u_of(last);
+        double* part = &A[0][0];
+        const int n0 = M.n0, j0 = w * n0 / N, j1 = (w + 1) * n0 / N;
+        auto pos = [&](int e) { return ((e % N3) << 6) + e / N3; };
+        for (int r = lane; r < n0; r += 64) {
+            double s = 0.0;
+#pragma unroll 8
+            for (int j = j0; j < j1; ++j) s = fma(M.inv[static_cast<int64_t>(j) * n0 + r], static_cast<double>(b[pos(j)]), s);
+            part[w * kTailUnknowns + r] = s;
+        }
+        tile_sync();
+        for (int r = w * 64 + lane; r < n0; r += 64 * N) {
+            double s = part[r];
+#pragma unroll
+            for (int k = 1; k < N; ++k) s += part[k * kTailUnknowns + r];
+            u[pos(r)] = static_cast<TS>(s);
+        }
+        tile_sync();
+    }
+#pragma unroll 1
+    for (int l = last - 1; l >= 0; --l) {
+        TS* u = u_of(l);
+        TS* t = t_of(l);
+        const TileCell<1> T(M.G[l], 0);
+        const MeshArgs& Gc = M.G[l + 1];
+        const TS* uc = u_of(l + 1) + (T.cx / 2 * Gc.my + T.cy / 2) * Gc.mz + T.cz / 2;
+        double v[N2];
+#pragma unroll
+        for (int q = 0; q < N2; ++q) v[q] = static_cast<double>(uc[(w * N2 + q) << 6]);
+        tile_kron<N>(M.P, T.cx & 1, T.cy & 1, T.cz & 1, w, lane, A, v);
+        if (T.valid) {
+#pragma unroll
+            for (int q = 0; q < N2; ++q) {
+                const int o = ((w * N2 + q) << 6) + lane;
+                t[o] = static_cast<TS>(static_cast<double>(u[o]) + v[q]);
+            }
+        }
+        tile_sync();
+#pragma unroll 1
+        for (int j = 0; j < 3; ++j) update(l, j == 1 ? u : t, j == 1 ? t : u, M.omega[j]);
+    }
+    const TileCell<1> T(M.G[0], 0);
+    if (T.valid) {
+#pragma unroll
+        for (int q = 0; q < N2; ++q) u0[((w * N2 + q) << 6) + lane] = ua[((w * N2 + q) << 6) + lane];
+    }
+}
 
 // Partial (a, b) per 64-cell tile (the layout of the PCG partials).
 template <int N, typename TS>
@@ -811,6 +967,15 @@ struct tp_mg {
 
 namespace {
 
+// Embeddings into the children and their transposes.
+template <int N>
+void prolongation_tables(const Plan& plan, ProlTab<N>& P, ProlTab<N>& PT) {
+    for (int i = 0; i < N * N; ++i) P.p[0][i] = plan.ref[N].P0[i], P.p[1][i] = plan.ref[N].P1[i];
+    for (int c = 0; c < 2; ++c)
+        for (int i = 0; i < N; ++i)
+            for (int j = 0; j < N; ++j) PT.p[c][i * N + j] = P.p[c][j * N + i];
+}
+
 template <int N, typename TI, bool HERM, typename TS>
 tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgState* st, hipStream_t s) {
     const Plan& plan = *m->plan;
@@ -823,13 +988,25 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
         return check_launch("coarse solve");
     }
     const TileTab<N, MgTC<TS>, HERM> R = tile_tab<N, MgTC<TS>, HERM>(plan, false);
+    if (L.G.ncells <= 64 && m->n0 <= kTailUnknowns) {   // (at most three levels: 64, 8 and 1 cells)
+        TailArgs<N, TI, HERM, TS> M;
+        M.levels = static_cast<int>(m->lv.size() - l);
+        M.n0 = static_cast<int>(m->n0);
+        M.R = R;
+        for (int i = 0; i < M.levels; ++i) {
+            M.G[i] = m->lv[l + i].G;
+            if (i + 1 < M.levels) M.E[i] = tile_inv<N, TI>(plan.ref[N], M.G[i], 1.0);
+        }
+        prolongation_tables<N>(plan, M.P, M.PT);
+        for (int j = 0; j < 3; ++j) M.omega[j] = m->omega[j];
+        M.inv = m->coarse_inv;
+        hipLaunchKernelGGL((k_mg_tail<N, TI, HERM, TS>), dim3(1), dim3(64, N), 0, s, b, u, M, st);
+        return check_launch("coarse levels");
+    }
     TileInv<N, TI> E[3];
     for (int j = 0; j < 3; ++j) E[j] = tile_inv<N, TI>(plan.ref[N], L.G, m->omega[j]);
     ProlTab<N> P, PT;
-    for (int i = 0; i < N * N; ++i) P.p[0][i] = plan.ref[N].P0[i], P.p[1][i] = plan.ref[N].P1[i];
-    for (int c = 0; c < 2; ++c)
-        for (int i = 0; i < N; ++i)
-            for (int j = 0; j < N; ++j) PT.p[c][i * N + j] = P.p[c][j * N + i];
+    prolongation_tables<N>(plan, P, PT);
     const bool pairs = tile_pairs(L.G, sizeof(TS), reinterpret_cast<uintptr_t>(b) % 16 == 0 &&
                                                        reinterpret_cast<uintptr_t>(u) % 16 == 0);
     // Chebyshev updates ping-pong between u and the level's scratch t; the
@@ -866,7 +1043,7 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
     if (stt != TP_OK) return stt;
     stt = vcycle_level<N, TI, HERM, TS>(m, l + 1, Cb, Cu, st, s);
     if (stt != TP_OK) return stt;
-    hipLaunchKernelGGL((k_mg_prolong<N, TS>), dim3(grid), dim3(64), 0, s, Cu, u, Lt, L.G, C.G, P, st);
+    hipLaunchKernelGGL((k_mg_prolong<N, TS>), dim3(grid), dim3(64, N), 0, s, Cu, u, Lt, L.G, C.G, P, st);
     step(Lt, u, 0);
     step(u, Lt, 1);
     step(Lt, u, 2);
@@ -893,10 +1070,7 @@ tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const 
     const TS* tabA = reinterpret_cast<const TS*>(eo_table(plan, N, EO_APPLY_A, sizeof(TS) == 8 ? 0 : 1));
     const TI* tabS = reinterpret_cast<const TI*>(eo_table(plan, N, EO_INV, sizeof(TI) == 8 ? 0 : 1));
     ProlTab<N> P, PT;
-    for (int i = 0; i < N * N; ++i) P.p[0][i] = plan.ref[N].P0[i], P.p[1][i] = plan.ref[N].P1[i];
-    for (int c = 0; c < 2; ++c)
-        for (int i = 0; i < N; ++i)
-            for (int j = 0; j < N; ++j) PT.p[c][i * N + j] = P.p[c][j * N + i];
+    prolongation_tables<N>(plan, P, PT);
     auto step = [&](const TS* from, TS* to, int j) {
         hipLaunchKernelGGL((k_mg_smooth_wave<N, TI, VP, TS>), dim3(grid), dim3(64), 0, s, b, from, to, L.G, tabA, F,
                            tabS, m->omega[j], st);
