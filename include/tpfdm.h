@@ -376,8 +376,9 @@ int32_t tp_plan_group_kernel(const tp_plan* plan, int32_t group, int32_t call, t
  * (TP_ERR_STATE).  tp_pcg_create allocates the solver's workspace (five
  * plan-sized FP64 vectors, the iterate included, and the reduction
  * partials); the plan must outlive it.  The first solve in each `inner`
- * precision captures a chunk of check_every iterations into a HIP graph that
- * later solves replay (iterations are enqueued as graph launches).  tp_pcg_solve: b, x device FP64 vectors in the plan's layout; x is the
+ * precision captures check_every iterations (with a V-cycle at most four) into
+ * a HIP graph that later solves replay (iterations are enqueued as graph
+ * launches).  tp_pcg_solve: b, x device FP64 vectors in the plan's layout; x is the
  * initial guess unless x_is_zero (then x is overwritten with zero first) and
  * holds the last iterate on return (x is written only at the end).  b = 0
  * with x_is_zero gives x = 0 at once; b = 0 with a non-zero guess cannot meet
@@ -385,9 +386,9 @@ int32_t tp_plan_group_kernel(const tp_plan* plan, int32_t group, int32_t call, t
  * the recursively updated residual r, or after maxit iterations
  * (TP_ERR_NOT_CONVERGED), or on a breakdown / non-finite value
  * (TP_ERR_NONFINITE).  Every iteration runs on the device without host
- * synchronisation; the host reads the solver state once per check_every
- * iterations (<= 0 selects 16), so up to check_every - 1 iterations' kernels
- * run after convergence and return at once.  Synchronises the stream before
+ * synchronisation; the host reads the solver state at least once per
+ * check_every iterations (<= 0 selects 16), so up to check_every - 1
+ * iterations' kernels run after convergence and return at once.  Synchronises the stream before
  * returning; summary (optional) receives the iterations, whether it
  * converged and the final relative residual.  One solve at a time per
  * solver object. */

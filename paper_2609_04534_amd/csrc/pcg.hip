@@ -617,9 +617,11 @@ struct tp_pcg {
     PcgState* host = nullptr;   // pinned host copy
     int64_t nwg = 0;
     int64_t elems = 0;
-    // one captured chunk of iterations per preconditioner precision (F64, F32)
+    // captured iterations per preconditioner precision (F64, F32): exec_chunk
+    // of them in a graph, `launches` graphs to a chunk of check_every
     hipGraphExec_t exec[2] = {nullptr, nullptr};
     int exec_chunk[2] = {0, 0};
+    int launches = 1;
     // non-blocking solves (tp_pcg_begin / tp_pcg_poll)
     hipEvent_t ev = nullptr;    // recorded after each enqueued step
     hipStream_t stream = nullptr;
@@ -643,8 +645,21 @@ void free_pcg(tp_pcg* s) {
     if (s->host) (void)hipHostFree(s->host);
 }
 
+// Iterations per captured graph for a chunk of check_every: all of them with
+// block-Jacobi (its iterations take tens of microseconds and solves hundreds of
+// them), and the largest divisor up to 4 with a V-cycle, whose solves take
+// about ten iterations of many launches each: graphs of 16 spent 0.4 of 1.65
+// ms (p = 2, 16^3 cells, 7 iterations) in launches after convergence, and their
+// instantiation costs a new solver more than a millisecond.
+int graph_iterations(int chunk, bool multigrid) {
+    if (!multigrid) return chunk;
+    for (int k = 4; k > 1; --k)
+        if (chunk % k == 0) return k;
+    return 1;
+}
+
 // Enqueues the start of a solve on stream (x = x0 or 0, r, z, p and the
-// first reduction) and makes sure the chunk graph of this precision exists.
+// first reduction) and makes sure the iteration graph of this precision exists.
 template <int N, typename TI, int LB>
 tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const double* b, const double* x,
                       bool x_zero, double rtol, int maxit, int chunk, hipStream_t stream) {
@@ -721,10 +736,12 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                        s->norm);
     tp_status st = check_launch("PCG start");
     if (st != TP_OK) return st;
-    // one chunk of iterations, captured once per solver and precision: every
-    // argument is solver-owned, so the graph replays for any b, x
+    // the iterations, captured once per solver and precision: every argument is
+    // solver-owned, so the graph replays for any b, x
     const int ti = sizeof(TI) == 8 ? 0 : 1;
-    if (!s->exec[ti] || s->exec_chunk[ti] != chunk) {
+    const int sub = graph_iterations(chunk, s->mg != nullptr);
+    s->launches = chunk / sub;
+    if (!s->exec[ti] || s->exec_chunk[ti] != sub) {
         if (s->exec[ti]) (void)hipGraphExecDestroy(s->exec[ti]), s->exec[ti] = nullptr;
         hipStream_t cs = nullptr;
         hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
@@ -732,7 +749,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
         hipGraph_t gr = nullptr;
         e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            for (int i = 0; i < chunk; ++i) {
+            for (int i = 0; i < sub; ++i) {
                 if constexpr (kLane) {
                     const dim3 wg(64, N), gr1(tile_grid(G, 1)), gr2(tile_grid(G, 2));
                     auto aq = [&](auto Hc) {
@@ -825,7 +842,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
             s->exec[ti] = nullptr;
             return hip_error(e, "PCG iteration graph");
         }
-        s->exec_chunk[ti] = chunk;
+        s->exec_chunk[ti] = sub;
     }
     s->ti = ti;
     return TP_OK;
@@ -951,15 +968,14 @@ tp_status tp_pcg_solve(tp_pcg* s, const double* b, double* x, int32_t x_is_zero,
     const int chunk = check_every > 0 ? check_every : 16;
     st = pcg_start(s, b, x, x_is_zero != 0, inner, rtol, maxit, chunk, stream);
     if (st != TP_OK) return st;
-    for (;;) {
+    do {   // (the kernels of a solve that is done after its start return at once)
+        hipError_t e = hipGraphLaunch(s->exec[s->ti], stream);
+        if (e != hipSuccess) return hip_error(e, "PCG iteration graph launch");
         st = enqueue_state_copy(s, stream);
         if (st != TP_OK) return st;
-        const hipError_t e = hipStreamSynchronize(stream);
+        e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return hip_error(e, "PCG state read-back");
-        if (s->host->done) break;
-        const hipError_t e2 = hipGraphLaunch(s->exec[s->ti], stream);
-        if (e2 != hipSuccess) return hip_error(e2, "PCG iteration graph launch");
-    }
+    } while (!s->host->done);
     st = enqueue_result_copy(s, x, stream);
     if (st != TP_OK) return st;
     const hipError_t e = hipStreamSynchronize(stream);
@@ -1012,7 +1028,8 @@ tp_status tp_pcg_poll(tp_pcg* s, tp_pcg_summary* summary) {
         st = enqueue_result_copy(s, s->xout, s->stream);
         if (st == TP_OK) s->phase = 2;
     } else {
-        const hipError_t e = hipGraphLaunch(s->exec[s->ti], s->stream);
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < s->launches && e == hipSuccess; ++i) e = hipGraphLaunch(s->exec[s->ti], s->stream);
         st = e == hipSuccess ? enqueue_state_copy(s, s->stream) : hip_error(e, "PCG iteration graph launch");
     }
     if (st == TP_OK) {
