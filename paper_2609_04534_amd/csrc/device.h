@@ -121,6 +121,62 @@ __device__ __forceinline__ void block_scales(const double* h, int64_t g, TC& sx,
     sz = static_cast<TC>(hx * hy / hz);
 }
 
+// One of a one-block tile's edge lengths per lane (lane d < 3: h_d), and the
+// block's scalings from them, uniform over the wave: the three divisions run
+// as one, lane d dividing for direction d.  (Every lane dividing three times
+// took a fifth of the VALU instructions of a tile at n = 8.)  Bit for bit
+// block_scales.  Every lane of the wave must call it.
+__device__ __forceinline__ double wave_lengths(const double* h, int64_t g) {
+    return h[3 * g + (threadIdx.x < 3 ? threadIdx.x : 0)];
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+template <typename TC>
+__device__ __forceinline__ void wave_scales(double len, TC& sx, TC& sy, TC& sz) {
+    const double hx = read_lane(len, 0), hy = read_lane(len, 1), hz = read_lane(len, 2);
+    const int d = threadIdx.x;
+    const double q = (d == 0 ? hy * hz : d == 1 ? hx * hz : hx * hy) / len;
+    sx = static_cast<TC>(read_lane(q, 0));
+    sy = static_cast<TC>(read_lane(q, 1));
+    sz = static_cast<TC>(read_lane(q, 2));
+}
+
+// Sum and maximum over the wave by an xor butterfly of lane distances 32, 16,
+// 8, 4, 2, 1 in registers (half-wave and row swaps, row rotations, quad
+// permutes; through LDS permutes the twelve steps of a residual's two norms
+// took longer than its arithmetic): every lane ends with the same value, bit
+// for bit (each step combines the same pair).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+template <typename Op>
+__device__ __forceinline__ double wave_butterfly(double v, Op op) {
+    {
+        const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v = op(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+    }
+    {
+        const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v = op(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+    }
+    v = op(v, dpp_move<0x128>(v));   // row rotation by 8
+    v = op(v, dpp_move<0x124>(v));   // row rotation by 4 (the row has period 8 here)
+    v = op(v, dpp_move<0x4e>(v));    // quad permute (2, 3, 0, 1)
+    return op(v, dpp_move<0xb1>(v));   // quad permute (1, 0, 3, 2)
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    return wave_butterfly(v, [](double a, double b) { return a + b; });
+}
+__device__ __forceinline__ double wave_max(double v) {
+    return wave_butterfly(v, [](double a, double b) { return fmax(a, b); });
+}
+
 // Reciprocal: hardware estimate refined by Newton-Raphson steps
 // r <- r + r (1 - a r), each of which roughly doubles the correct bits.
 __device__ __forceinline__ double recip(double a) {
@@ -169,13 +225,16 @@ struct Pencil {
     int w;       // block within the tile
     int pa, pb;  // pencil coordinates (meaning depends on the phase)
     bool act;    // lane owns a pencil of an existing block
+    // n = 8: a tile is one block (there is always one) and every lane has a pencil
+    static constexpr bool kFull = Slab<N>::N2 == 64;
     __device__ __forceinline__ Pencil(int nvalid) {
         const int lane = threadIdx.x;
         w = lane / Slab<N>::N2;
         const int p = lane - w * Slab<N>::N2;
         pa = p / N;
         pb = p - pa * N;
-        act = w < Slab<N>::BPW && w < nvalid;
+        if (kFull) w = 0;
+        act = kFull || (w < Slab<N>::BPW && w < nvalid);
     }
 };
 

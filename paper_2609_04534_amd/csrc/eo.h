@@ -15,6 +15,38 @@ struct EOShape {
     static constexpr int SO = H * H;
 };
 
+// A 1D table in device memory read at wave-uniform addresses (scalar loads).
+// fresh() makes the address opaque at each use: M and P of n = 7 and 8 in FP64
+// (100 and 128 scalar registers) do not fit, and values loaded for one
+// contraction and kept for the next are spilled to vector lanes, a VALU
+// instruction each way (470 reads of them in the n = 8 solve).
+template <typename T>
+struct UniTab {
+    const T* p;
+    __device__ __forceinline__ UniTab operator+(int i) const { return UniTab{p + i}; }
+};
+template <int N, typename T>
+__device__ __forceinline__ auto fresh(UniTab<T> t) {
+    if constexpr (N >= 7 && sizeof(T) == 8) {
+        auto p = (const T __attribute__((address_space(4)))*)t.p;   // (constant: scalar loads)
+        asm volatile("" : "+s"(p));
+        return p;
+    } else {
+        return t.p;
+    }
+}
+template <int N, typename T>
+__device__ __forceinline__ const T* fresh(const T* p) {
+    return p;
+}
+
+// The table in device memory (SCALAR) or its copy in registers.
+template <bool SCALAR, typename T>
+__device__ __forceinline__ auto table_of(const T* tab, const T* regs) {
+    if constexpr (SCALAR) return UniTab<T>{tab};
+    else return regs;
+}
+
 // e, o parts of a pencil.
 template <int N, typename T>
 __device__ __forceinline__ void eo_split(const T (&x)[N], T (&e)[EOShape<N>::HC], T (&o)[EOShape<N>::H]) {
@@ -28,23 +60,25 @@ __device__ __forceinline__ void eo_split(const T (&x)[N], T (&e)[EOShape<N>::HC]
 }
 
 // E = AE e (HC outputs), O = AO o (H outputs); matrices row-major.
-template <int N, typename T>
-__device__ __forceinline__ void eo_mul(const T* AE, const T* AO, const T (&e)[EOShape<N>::HC],
+template <int N, typename T, typename Tab>
+__device__ __forceinline__ void eo_mul(Tab tE, Tab tO, const T (&e)[EOShape<N>::HC],
                                        const T (&o)[EOShape<N>::H], T (&E)[EOShape<N>::HC],
                                        T (&O)[EOShape<N>::H]) {
+    const auto AE = fresh<N>(tE);
+    const auto AO = fresh<N>(tO);
     constexpr int H = EOShape<N>::H, HC = EOShape<N>::HC;
 #pragma unroll
     for (int i = 0; i < HC; ++i) {
-        T s = T(0);
+        T s = AE[i * HC] * e[0];
 #pragma unroll
-        for (int j = 0; j < HC; ++j) s = fma(AE[i * HC + j], e[j], s);
+        for (int j = 1; j < HC; ++j) s = fma(AE[i * HC + j], e[j], s);
         E[i] = s;
     }
 #pragma unroll
     for (int i = 0; i < H; ++i) {
-        T s = T(0);
+        T s = AO[i * H] * o[0];
 #pragma unroll
-        for (int j = 0; j < H; ++j) s = fma(AO[i * H + j], o[j], s);
+        for (int j = 1; j < H; ++j) s = fma(AO[i * H + j], o[j], s);
         O[i] = s;
     }
 }
@@ -63,44 +97,48 @@ __device__ __forceinline__ void eo_join(const T (&E)[EOShape<N>::HC], const T (&
 // Forward spectral transform y = S^T x along a pencil: the first HC outputs
 // are the coefficients of the symmetric eigenvectors, the last H those of
 // the antisymmetric ones (SE[k][c] = S[k][sym c] for k < HC, SO likewise).
-template <int N, typename T>
-__device__ __forceinline__ void eo_fwd(const T* SE, const T* SO, const T (&x)[N], T (&y)[N]) {
+template <int N, typename T, typename Tab>
+__device__ __forceinline__ void eo_fwd(Tab tE, Tab tO, const T (&x)[N], T (&y)[N]) {
+    const auto SE = fresh<N>(tE);
+    const auto SO = fresh<N>(tO);
     constexpr int H = EOShape<N>::H, HC = EOShape<N>::HC;
     T e[HC], o[H];
     eo_split<N>(x, e, o);
 #pragma unroll
     for (int c = 0; c < HC; ++c) {
-        T s = T(0);
+        T s = SE[c] * e[0];
 #pragma unroll
-        for (int k = 0; k < HC; ++k) s = fma(SE[k * HC + c], e[k], s);
+        for (int k = 1; k < HC; ++k) s = fma(SE[k * HC + c], e[k], s);
         y[c] = s;
     }
 #pragma unroll
     for (int c = 0; c < H; ++c) {
-        T s = T(0);
+        T s = SO[c] * o[0];
 #pragma unroll
-        for (int k = 0; k < H; ++k) s = fma(SO[k * H + c], o[k], s);
+        for (int k = 1; k < H; ++k) s = fma(SO[k * H + c], o[k], s);
         y[HC + c] = s;
     }
 }
 
 // Backward transform x = S y (y in the split spectral order of eo_fwd).
-template <int N, typename T>
-__device__ __forceinline__ void eo_bwd(const T* SE, const T* SO, const T (&y)[N], T (&x)[N]) {
+template <int N, typename T, typename Tab>
+__device__ __forceinline__ void eo_bwd(Tab tE, Tab tO, const T (&y)[N], T (&x)[N]) {
+    const auto SE = fresh<N>(tE);
+    const auto SO = fresh<N>(tO);
     constexpr int H = EOShape<N>::H, HC = EOShape<N>::HC;
     T E[HC], O[H];
 #pragma unroll
     for (int k = 0; k < HC; ++k) {
-        T s = T(0);
+        T s = SE[k * HC] * y[0];
 #pragma unroll
-        for (int c = 0; c < HC; ++c) s = fma(SE[k * HC + c], y[c], s);
+        for (int c = 1; c < HC; ++c) s = fma(SE[k * HC + c], y[c], s);
         E[k] = s;
     }
 #pragma unroll
     for (int k = 0; k < H; ++k) {
-        T s = T(0);
+        T s = SO[k * H] * y[HC];
 #pragma unroll
-        for (int c = 0; c < H; ++c) s = fma(SO[k * H + c], y[HC + c], s);
+        for (int c = 1; c < H; ++c) s = fma(SO[k * H + c], y[HC + c], s);
         O[k] = s;
     }
     eo_join<N>(E, O, x);
@@ -199,10 +237,10 @@ __device__ __forceinline__ void stage_table(const TC* __restrict__ tab, TC* stab
 // registers and synchronises the wave between phases.
 
 // v = A x (global output).  A1, A2: the lane's LDS scratch slabs.
-template <int N, typename TS, typename TC>
+template <int N, typename TS, typename TC, typename Tab>
 __device__ __forceinline__ void eo_apply_body(const Pencil<N>& pc, const TC (&x)[N], TS* __restrict__ v,
-                                              const GArgs& G, int64_t g0, TC* A1, TC* A2, const TC* ME,
-                                              const TC* MO, const TC* PE, const TC* PO, TC sx, TC sy, TC sz) {
+                                              const GArgs& G, int64_t g0, TC* A1, TC* A2, Tab ME,
+                                              Tab MO, Tab PE, Tab PO, TC sx, TC sy, TC sz) {
     using L = Slab<N>;
     constexpr int HC = EOShape<N>::HC, H = EOShape<N>::H;
     const int pa = pc.pa, pb = pc.pb;
@@ -274,8 +312,8 @@ __device__ __forceinline__ void eo_apply_body(const Pencil<N>& pc, const TC (&x)
 // The three middle phases of D^{-1} on the lane's slab A1, which on entry
 // holds S_z^T applied along z; on exit A1 holds S_y S_x Lambda^{-1} ... along
 // every axis but z (backward z is left to the caller).
-template <int N, typename TC>
-__device__ __forceinline__ void eo_inverse_mid(const Pencil<N>& pc, TC* A1, const TC* SE, const TC* SO,
+template <int N, typename TC, typename Tab>
+__device__ __forceinline__ void eo_inverse_mid(const Pencil<N>& pc, TC* A1, Tab SE, Tab SO,
                                                const TC* lam, TC sx, TC sy, TC sz) {
     using L = Slab<N>;
     const int pa = pc.pa, pb = pc.pb;
@@ -318,9 +356,9 @@ __device__ __forceinline__ void eo_inverse_mid(const Pencil<N>& pc, TC* A1, cons
 // backward, then z and x backward: the last phase is along x, whose lanes
 // (j, k) write consecutive addresses of an x-plane (whole 128-byte lines for
 // n = 8 at every storage type and n = 4 in FP64), like the apply's output.
-template <int N, bool VP, typename TS, typename TC>
+template <int N, bool VP, typename TS, typename TC, typename Tab>
 __device__ __forceinline__ void eo_inverse_body(const Pencil<N>& pc, const TC (&r)[N], TS* __restrict__ x,
-                                                const GArgs& G, int64_t g0, TC* A1, const TC* SE, const TC* SO,
+                                                const GArgs& G, int64_t g0, TC* A1, Tab SE, Tab SO,
                                                 const TC* lam, TC sx, TC sy, TC sz) {
     using L = Slab<N>;
     const int pa = pc.pa, pb = pc.pb;
@@ -382,9 +420,9 @@ __device__ __forceinline__ void eo_inverse_body(const Pencil<N>& pc, const TC (&
 // dst = A x with the lane's z-pencil of x in registers, through LDS (dst
 // may alias t1); t1, t2 scratch slabs.  dst receives the product in slab
 // layout, written by x-pencils; the wave is synchronised on return.
-template <int N, typename TC>
+template <int N, typename TC, typename Tab>
 __device__ __forceinline__ void eo_apply_regs(const Pencil<N>& pc, const TC (&x)[N], TC* dst, TC* t1, TC* t2,
-                                              const TC* ME, const TC* MO, const TC* PE, const TC* PO, TC sx, TC sy,
+                                              Tab ME, Tab MO, Tab PE, Tab PO, TC sx, TC sy,
                                               TC sz) {
     using L = Slab<N>;
     constexpr int HC = EOShape<N>::HC, H = EOShape<N>::H;
@@ -448,9 +486,9 @@ __device__ __forceinline__ void eo_apply_regs(const Pencil<N>& pc, const TC (&x)
 
 // r <- D^{-1} r with the lane's z-pencil of r in registers on entry and on
 // return, through the LDS slab (each phase updates its own pencils).
-template <int N, typename TC>
-__device__ __forceinline__ void eo_inverse_regs(const Pencil<N>& pc, TC (&r)[N], TC* slab, const TC* SE,
-                                                const TC* SO, const TC* lam, TC sx, TC sy, TC sz) {
+template <int N, typename TC, typename Tab>
+__device__ __forceinline__ void eo_inverse_regs(const Pencil<N>& pc, TC (&r)[N], TC* slab, Tab SE,
+                                                Tab SO, const TC* lam, TC sx, TC sy, TC sz) {
     using L = Slab<N>;
     const int pa = pc.pa, pb = pc.pb;
     if (pc.act) {
@@ -471,8 +509,8 @@ __device__ __forceinline__ void eo_inverse_regs(const Pencil<N>& pc, TC (&r)[N],
 }
 
 // slab <- D^{-1} slab entirely in LDS (each phase updates its own pencils).
-template <int N, typename TC>
-__device__ __forceinline__ void eo_inverse_lds(const Pencil<N>& pc, TC* slab, const TC* SE, const TC* SO,
+template <int N, typename TC, typename Tab>
+__device__ __forceinline__ void eo_inverse_lds(const Pencil<N>& pc, TC* slab, Tab SE, Tab SO,
                                                const TC* lam, TC sx, TC sy, TC sz) {
     using L = Slab<N>;
     TC a[N];
@@ -624,27 +662,15 @@ __device__ __forceinline__ void solve_tile(const double* __restrict__ b, double*
     wave_sync();
 }
 
-// Sum and maximum over the wave by an xor butterfly: every lane ends with
-// the same value, bit for bit (each step adds or compares the same pair).
-__device__ __forceinline__ double wave_allsum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ double wave_allmax(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 // LDS workspace of the register-resident solve tile: two FP64 scratch
 // slabs for the product (the first also holds the inner solve's slab, in
 // the inner precision) and the per-block reductions.
 template <int N>
 struct SolveLdsR {
     static constexpr int SZ = Slab<N>::BPW * Slab<N>::size;
+    static constexpr bool kOne = Slab<N>::BPW == 1;   // one-block tiles reduce over the wave
     double t1[SZ], t2[SZ];
-    double part[2][64];
+    double part[2][kOne ? 1 : 64];
     double red[3][Slab<N>::BPW];
     int done[Slab<N>::BPW];
 };
@@ -692,7 +718,7 @@ __device__ __forceinline__ void solve_tile_reg(const double* __restrict__ b, dou
     constexpr bool kOne = L::BPW == 1;
     double bn;
     if constexpr (kOne) {
-        bn = wave_allsum(bsq);
+        bn = wave_sum(bsq);
     } else {
         S.part[0][lane] = bsq;
         wave_sync();
@@ -731,8 +757,8 @@ __device__ __forceinline__ void solve_tile_reg(const double* __restrict__ b, dou
         double rsq_b, rmax_b;
         bool mine_done = true;
         if constexpr (kOne) {
-            rsq_b = wave_allsum(rr);
-            rmax_b = wave_allmax(rmax);
+            rsq_b = wave_sum(rr);
+            rmax_b = wave_max(rmax);
             if (!done_before) {
                 rel = bn == 0.0 ? 0.0 : sqrt(rsq_b / bn);
                 mine_done = !(rel > rtol) || it >= maxit;
@@ -807,8 +833,7 @@ struct InvTab {
 // The solve tile with the even-odd reference operators: per-block scalings
 // from the edge lengths, iterate and residual in registers
 // (solve_tile_reg).  tA: the apply table ME|MO|PE|PO (FP64), tS: the inverse
-// table SE|SO (TI), lam: the eigenvalues (TI); each may point to registers
-// or to LDS.
+// table SE|SO (TI), both in device memory; lam: the eigenvalues (TI).
 template <int N, typename TI, int RND, bool VP>
 __device__ __forceinline__ void eo_solve_tile(const double* __restrict__ b, double* __restrict__ x, const GArgs& G,
                                               int64_t g0, int nvalid, SolveLdsR<N>& S, const double* tA,
@@ -817,17 +842,20 @@ __device__ __forceinline__ void eo_solve_tile(const double* __restrict__ b, doub
                                               int64_t block0, SolveAcc& acc) {
     using E = EOShape<N>;
     const Pencil<N> pc(nvalid);
+    const UniTab<double> A{tA};
+    const UniTab<TI> I{tS};
     double sx = 1.0, sy = 1.0, sz = 1.0;
-    if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
+    if constexpr (Slab<N>::BPW == 1) wave_scales(wave_lengths(G.h, g0), sx, sy, sz);
+    else if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
     const TI sxi = static_cast<TI>(sx), syi = static_cast<TI>(sy), szi = static_cast<TI>(sz);
     solve_tile_reg<N, TI, RND, VP>(
         b, x, G, g0, nvalid, S,
         [&](const Pencil<N>& p, const double (&xr)[N], double* dst, double* t1, double* t2) {
-            eo_apply_regs<N, double>(p, xr, dst, t1, t2, tA, tA + E::SE, tA + E::SE + E::SO, tA + 2 * E::SE + E::SO,
+            eo_apply_regs<N, double>(p, xr, dst, t1, t2, A, A + E::SE, A + (E::SE + E::SO), A + (2 * E::SE + E::SO),
                                      sx, sy, sz);
         },
         [&](const Pencil<N>& p, TI (&d)[N], TI* slab) {
-            eo_inverse_regs<N, TI>(p, d, slab, tS, tS + E::SE, lam, sxi, syi, szi);
+            eo_inverse_regs<N, TI>(p, d, slab, I, I + E::SE, lam, sxi, syi, szi);
         },
         rtol, maxit, iters, relres, block0, acc);
 }

@@ -52,11 +52,10 @@ __global__ __launch_bounds__(64, 2) void k_apply_eo(const TS* __restrict__ u, TS
     __shared__ TC stab[kScalarTab ? 1 : TAB];
     TC T[kScalarTab ? 1 : TAB];
     if constexpr (!kScalarTab) load_table<TC, TAB>(T, tab, stab);
-    const TC* Tb = kScalarTab ? tab : T;
-    const TC* ME = Tb;
-    const TC* MO = Tb + S::SE;
-    const TC* PE = Tb + S::SE + S::SO;
-    const TC* PO = Tb + 2 * S::SE + S::SO;
+    const auto ME = table_of<kScalarTab, TC>(tab, T);
+    const auto MO = ME + S::SE;
+    const auto PE = ME + (S::SE + S::SO);
+    const auto PO = ME + (2 * S::SE + S::SO);
     int64_t t = blockIdx.x;
     if (t >= ntiles) return;
     const int lane = threadIdx.x;
@@ -71,6 +70,8 @@ __global__ __launch_bounds__(64, 2) void k_apply_eo(const TS* __restrict__ u, TS
         const bool ok = lw < L::BPW && lw < nvalid_of<N>(G, t);
         if (ok) pencil_load<N, VP>(pre, pencil_ptr<N>(u, G, t * L::BPW + lw, li, lj), G.logB);
     }
+    constexpr bool kOne = L::BPW == 1;
+    double len = kOne ? wave_lengths(G.h, t < ntiles ? t : 0) : 0.0;
     for (; t < ntiles; t += gridDim.x) {
         const int64_t g0 = t * L::BPW;
         const Pencil<N> pc(nvalid_of<N>(G, t));
@@ -81,7 +82,13 @@ __global__ __launch_bounds__(64, 2) void k_apply_eo(const TS* __restrict__ u, TS
         if (tn < ntiles && lw < L::BPW && lw < nvalid_of<N>(G, tn))
             pencil_load<N, VP>(pre, pencil_ptr<N>(u, G, tn * L::BPW + lw, li, lj), G.logB);
         TC sx = TC(1), sy = TC(1), sz = TC(1);
-        if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
+        if constexpr (kOne) {
+            const double cur = len;
+            if (tn < ntiles) len = wave_lengths(G.h, tn);
+            wave_scales(cur, sx, sy, sz);
+        } else if (pc.act) {
+            block_scales(G.h, g0 + pc.w, sx, sy, sz);
+        }
         eo_apply_body<N>(pc, x, v, G, g0, A1, A2, ME, MO, PE, PO, sx, sy, sz);
     }
 }
@@ -107,8 +114,8 @@ __global__ __launch_bounds__(64, 2) void k_inverse_eo(const TS* __restrict__ r, 
 #pragma unroll
         for (int i = 0; i < TABM; ++i) T[i] = tab[i];
     }
-    const TC* SE = kScalarTab ? tab : T;
-    const TC* SO = (kScalarTab ? tab : T) + S::SE;
+    const TC* SE = kScalarTab ? tab : T;   // (64 scalar registers at n = 8 in FP64: they fit)
+    const TC* SO = SE + S::SE;
     const TC* lam = stab + TABM;
     int64_t t = blockIdx.x;
     if (t >= ntiles) return;
@@ -123,6 +130,8 @@ __global__ __launch_bounds__(64, 2) void k_inverse_eo(const TS* __restrict__ r, 
         const bool ok = lw < L::BPW && lw < nvalid_of<N>(G, t);
         if (ok) pencil_load<N, VP>(pre, pencil_ptr<N>(r, G, t * L::BPW + lw, li, lj), G.logB);
     }
+    constexpr bool kOne = L::BPW == 1;
+    double len = kOne ? wave_lengths(G.h, t < ntiles ? t : 0) : 0.0;
     for (; t < ntiles; t += gridDim.x) {
         const int64_t g0 = t * L::BPW;
         const Pencil<N> pc(nvalid_of<N>(G, t));
@@ -133,7 +142,13 @@ __global__ __launch_bounds__(64, 2) void k_inverse_eo(const TS* __restrict__ r, 
         if (tn < ntiles && lw < L::BPW && lw < nvalid_of<N>(G, tn))
             pencil_load<N, VP>(pre, pencil_ptr<N>(r, G, tn * L::BPW + lw, li, lj), G.logB);
         TC sx = TC(1), sy = TC(1), sz = TC(1);
-        if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
+        if constexpr (kOne) {
+            const double cur = len;
+            if (tn < ntiles) len = wave_lengths(G.h, tn);
+            wave_scales(cur, sx, sy, sz);
+        } else if (pc.act) {
+            block_scales(G.h, g0 + pc.w, sx, sy, sz);
+        }
         eo_inverse_body<N, VP>(pc, xin, x, G, g0, A1, SE, SO, lam, sx, sy, sz);
     }
 }

@@ -15,13 +15,6 @@ struct PcgState {
     int norm;   // stopping test on 0: (r, r), 1: (r, z) (tol2 scaled to match)
 };
 
-// Sum of a double over the 64 lanes of a wave.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
 struct MeshArgs {
     int64_t ncells;
     int64_t offset;

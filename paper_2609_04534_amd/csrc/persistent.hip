@@ -112,7 +112,8 @@ __device__ __forceinline__ void seg_apply_wave(const TS* __restrict__ u, TS* __r
         TC x[N];
         if (lw < L::BPW && lw < nvalid) pencil_load<N, VP>(x, pencil_ptr<N>(u, G, g0 + lw, li, lj), G.logB);
         TC sx = TC(1), sy = TC(1), sz = TC(1);
-        if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
+        if constexpr (L::BPW == 1) wave_scales(wave_lengths(G.h, g0), sx, sy, sz);
+        else if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
         eo_apply_body<N>(pc, x, v, G, g0, s1 + so, s2 + so, A.ME(), A.MO(), A.PE(), A.PO(), sx, sy, sz);
     }
 }
@@ -188,7 +189,8 @@ __device__ __forceinline__ void seg_inverse_wave(const TS* __restrict__ r, TS* _
         TC xin[N];
         if (lw < L::BPW && lw < nvalid) pencil_load<N, VP>(xin, pencil_ptr<N>(r, G, g0 + lw, li, lj), G.logB);
         TC sx = TC(1), sy = TC(1), sz = TC(1);
-        if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
+        if constexpr (L::BPW == 1) wave_scales(wave_lengths(G.h, g0), sx, sy, sz);
+        else if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
         eo_inverse_body<N, VP>(pc, xin, x, G, g0, s1 + so, I.SE(), I.SO(), lam, sx, sy, sz);
     }
 }
