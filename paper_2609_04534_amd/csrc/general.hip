@@ -12,6 +12,14 @@
 // factors staged once in LDS and read there with per-block broadcast
 // addresses, the block slab in LDS between the direction phases.
 //
+// The apply and the inverse are bound by memory: each block's factors are read
+// once for its one product (768 bytes beside 1 KiB of operands at n = 4 in
+// FP64).  With a workgroup per tile there is no loop to wait in: other tiles'
+// loads run while one computes, and a tile's operands are requested before its
+// factors are staged.  20011 blocks of n = 4, FP64, product and inverse
+// together: 27.7 us with 16 workgroups a CU looping over the tiles and the
+// factors of a tile unpadded, 21.3 us so; 43.6 -> 21.2 us for a drawn n = 3.
+//
 // Device layouts (plan-owned):
 //   fac[b][d][0 = M, 1 = P][n][n]          row-major
 //   eig[b][d][ S[n][n] (column c = eigenvector c) | lam[n] ]
@@ -28,6 +36,15 @@ struct GenShape {
     static constexpr int F = 6 * N * N;        // factor entries per block
     static constexpr int E = 3 * (N * N + N);  // eigen entries per block
 };
+
+// Entries between two blocks' factors in LDS: `count` rounded up to an odd
+// number of 16-byte units.  The lanes of a tile's blocks read one entry each
+// at this distance; at n = 4 in FP64 (768 bytes) all four were in one bank.
+template <typename T, int COUNT>
+constexpr int lds_stride() {
+    constexpr int u = 16 / static_cast<int>(sizeof(T));
+    return ((COUNT + u - 1) / u | 1) * u;
+}
 
 // y = A x and y = A^T x for a row-major N x N matrix in LDS.
 template <int N, typename T>
@@ -51,20 +68,19 @@ __device__ __forceinline__ void mvt(const T* A, const T (&x)[N], T (&y)[N]) {
     }
 }
 
-// dst = A src on the lane's block slab, A the Kronecker sum of the block's
-// factors F (in LDS); dst may alias src; t1, t2 scratch slabs.
-//   z: t = M_z src, w = P_z src;  y: a = M_y t, b = P_y t + M_y w;
-//   x: dst = P_x a + M_x b.
+// y = A x for the lane's block, A the Kronecker sum of the block's factors F
+// (in LDS): x the lane's z-pencil, y its x-pencil; t1, t2 scratch slabs.
+//   z: t = M_z x, w = P_z x;  y: a = M_y t, b = P_y t + M_y w;
+//   x: y = P_x a + M_x b.
 template <int N, typename T>
-__device__ __forceinline__ void gen_apply_lds(const Pencil<N>& pc, const T* src, T* dst, T* t1, T* t2, const T* F) {
+__device__ __forceinline__ void gen_apply_regs(const Pencil<N>& pc, const T (&x)[N], T (&out)[N], T* t1, T* t2,
+                                               const T* F) {
     using L = Slab<N>;
     constexpr int N2 = N * N;
     const T *Mx = F, *Px = F + N2, *My = F + 2 * N2, *Py = F + 3 * N2, *Mz = F + 4 * N2, *Pz = F + 5 * N2;
     const int pa = pc.pa, pb = pc.pb;
     if (pc.act) {
-        T x[N], y[N];
-#pragma unroll
-        for (int k = 0; k < N; ++k) x[k] = src[L::at(pa, pb, k)];
+        T y[N];
         mv<N>(Mz, x, y);
 #pragma unroll
         for (int k = 0; k < N; ++k) t1[L::at(pa, pb, k)] = y[k];
@@ -100,24 +116,38 @@ __device__ __forceinline__ void gen_apply_lds(const Pencil<N>& pc, const T* src,
         mv<N>(Px, a, y1);
         mv<N>(Mx, b, y2);
 #pragma unroll
-        for (int i = 0; i < N; ++i) dst[L::at(i, pa, pb)] = y1[i] + y2[i];
+        for (int i = 0; i < N; ++i) out[i] = y1[i] + y2[i];
+    }
+}
+
+// dst = A src on the lane's block slab; dst may alias src or t1.
+template <int N, typename T>
+__device__ __forceinline__ void gen_apply_lds(const Pencil<N>& pc, const T* src, T* dst, T* t1, T* t2, const T* F) {
+    using L = Slab<N>;
+    T x[N], y[N];
+    if (pc.act) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) x[k] = src[L::at(pc.pa, pc.pb, k)];
+    }
+    gen_apply_regs<N, T>(pc, x, y, t1, t2, F);
+    if (pc.act) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) dst[L::at(i, pc.pa, pc.pb)] = y[i];
     }
     wave_sync();
 }
 
-// slab <- D^{-1} slab with the block's eigen-decompositions E (in LDS):
-// S_z^T, S_y^T, S_x^T, scaling by 1/(lam_x[i] + lam_y[j] + lam_z[k]),
-// S_x, S_y, S_z, each phase on its own pencils.
+// a <- D^{-1} a with the block's eigen-decompositions E (in LDS), a the lane's
+// z-pencil: S_z^T, S_y^T, S_x^T, scaling by 1/(lam_x[i] + lam_y[j] +
+// lam_z[k]), S_x, S_y, S_z, each phase on its own pencils of the slab.
 template <int N, typename T>
-__device__ __forceinline__ void gen_inverse_lds(const Pencil<N>& pc, T* slab, const T* E) {
+__device__ __forceinline__ void gen_inverse_regs(const Pencil<N>& pc, T (&a)[N], T* slab, const T* E) {
     using L = Slab<N>;
     constexpr int NE = N * N + N;
     const T *Sx = E, *lx = E + N * N, *Sy = E + NE, *ly = E + NE + N * N, *Sz = E + 2 * NE, *lz = E + 2 * NE + N * N;
     const int pa = pc.pa, pb = pc.pb;
-    T a[N], y[N];
+    T y[N];
     if (pc.act) {  // z forward
-#pragma unroll
-        for (int k = 0; k < N; ++k) a[k] = slab[L::at(pa, pb, k)];
         mvt<N>(Sz, a, y);
 #pragma unroll
         for (int c = 0; c < N; ++c) slab[L::at(pa, pb, c)] = y[c];
@@ -155,81 +185,91 @@ __device__ __forceinline__ void gen_inverse_lds(const Pencil<N>& pc, T* slab, co
 #pragma unroll
         for (int c = 0; c < N; ++c) y[c] = slab[L::at(pa, pb, c)];
         mv<N>(Sz, y, a);
+    }
+}
+
+// slab <- D^{-1} slab.
+template <int N, typename T>
+__device__ __forceinline__ void gen_inverse_lds(const Pencil<N>& pc, T* slab, const T* E) {
+    using L = Slab<N>;
+    T a[N];
+    if (pc.act) {
 #pragma unroll
-        for (int k = 0; k < N; ++k) slab[L::at(pa, pb, k)] = a[k];
+        for (int k = 0; k < N; ++k) a[k] = slab[L::at(pc.pa, pc.pb, k)];
+    }
+    gen_inverse_regs<N, T>(pc, a, slab, E);
+    if (pc.act) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) slab[L::at(pc.pa, pc.pb, k)] = a[k];
     }
     wave_sync();
 }
 
-// Copies `count` consecutive elements starting at src into LDS.
-template <typename T>
-__device__ __forceinline__ void stage(T* dst, const T* __restrict__ src, int count) {
-    for (int e = threadIdx.x; e < count; e += 64) dst[e] = src[e];
+// Copies the COUNT entries of each of nvalid consecutive blocks into LDS, ST
+// entries apart.
+template <int COUNT, int ST, typename T>
+__device__ __forceinline__ void stage(T* dst, const T* __restrict__ src, int nvalid) {
+    for (int e = threadIdx.x; e < nvalid * COUNT; e += 64) dst[e / COUNT * ST + e % COUNT] = src[e];
 }
 
-// The tile's input z-pencils into the slab (storage -> compute type).
-template <int N, bool VP, typename TS, typename TC>
-__device__ __forceinline__ void slab_in(const Pencil<N>& pc, TC* slab, const TS* __restrict__ u, const GArgs& G,
-                                        int64_t g0) {
-    using L = Slab<N>;
-    if (pc.act) {
-        TC x[N];
-        pencil_load<N, VP>(x, pencil_ptr<N>(u, G, g0 + pc.w, pc.pa, pc.pb), G.logB);
-#pragma unroll
-        for (int k = 0; k < N; ++k) slab[L::at(pc.pa, pc.pb, k)] = x[k];
-    }
-}
-
+// The workgroups of both kernels take the tiles from tile0 on, those that one
+// XCD runs in a row.
 template <int N, typename TS, typename TC, bool VP>
 __global__ __launch_bounds__(64, 2) void k_apply_gen(const TS* __restrict__ u, TS* __restrict__ v, GArgs G,
-                                                     const TC* __restrict__ fac, int64_t ntiles) {
+                                                     const TC* __restrict__ fac, int64_t tile0) {
     using L = Slab<N>;
-    constexpr int F = GenShape<N>::F;
-    __shared__ TC sf[L::BPW * F];
-    __shared__ TC s0[L::BPW * L::size], s1[L::BPW * L::size], s2[L::BPW * L::size];
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const int64_t g0 = t * L::BPW;
-        const int nvalid = nvalid_of<N>(G, t);
-        const Pencil<N> pc(nvalid);
-        const int so = (pc.w < L::BPW ? pc.w : 0) * L::size;
-        stage(sf, fac + g0 * F, nvalid * F);
-        slab_in<N, VP, TS, TC>(pc, s0 + so, u, G, g0);
-        wave_sync();
-        gen_apply_lds<N, TC>(pc, s0 + so, s0 + so, s1 + so, s2 + so, sf + (pc.w < L::BPW ? pc.w : 0) * F);
-        if (pc.act) {  // x-planes to global memory: lanes (j, k) of a plane are consecutive
-            TS* out = v + G.offset + block_base(g0 + pc.w, G.logB, L::N3);
+    constexpr int F = GenShape<N>::F, FS = lds_stride<TC, F>();
+    __shared__ __align__(16) TC sf[L::BPW * FS];
+    __shared__ TC s1[L::BPW * L::size], s2[L::BPW * L::size];
+    const XcdRange r = xcd_range(blockIdx.x, gridDim.x);
+    const int64_t t = tile0 + r.first + r.place;
+    const int64_t g0 = t * L::BPW;
+    const int nvalid = nvalid_of<N>(G, t);
+    const Pencil<N> pc(nvalid);
+    const int so = (pc.w < L::BPW ? pc.w : 0) * L::size;
+    TC x[N];
+    if (pc.act) pencil_load<N, VP>(x, pencil_ptr<N>(u, G, g0 + pc.w, pc.pa, pc.pb), G.logB);
+    stage<F, FS>(sf, fac + g0 * F, nvalid);
+    wave_sync();
+    TC y[N];
+    gen_apply_regs<N, TC>(pc, x, y, s1 + so, s2 + so, sf + (pc.w < L::BPW ? pc.w : 0) * FS);
+    if (pc.act) {  // x-planes to global memory: lanes (j, k) of a plane are consecutive
+        TS* out = v + G.offset + block_base(g0 + pc.w, G.logB, L::N3);
 #pragma unroll
-            for (int i = 0; i < N; ++i)
-                stc(out + (static_cast<int64_t>((i * N + pc.pa) * N + pc.pb) << G.logB), s0[so + L::at(i, pc.pa, pc.pb)]);
-        }
-        wave_sync();
+        for (int i = 0; i < N; ++i)
+            stc(out + (static_cast<int64_t>((i * N + pc.pa) * N + pc.pb) << G.logB), y[i]);
     }
 }
 
+// Waves per SIMD of the inverse: 4 (n = 7 in FP64 else takes 138 registers and
+// runs 3: 59.5 -> 54.8 us for 20000 blocks), at n = 8 in FP64 3, which it
+// reaches when the phases' lane test is not folded away (75.0 -> 65.4 us).
+template <int N, typename TC>
+constexpr int inverse_waves() {
+    return N == 8 && sizeof(TC) == 8 ? 3 : 4;
+}
+
 template <int N, typename TS, typename TC, bool VP>
-__global__ __launch_bounds__(64, 2) void k_inverse_gen(const TS* __restrict__ r, TS* __restrict__ x, GArgs G,
-                                                       const TC* __restrict__ eig, int64_t ntiles) {
+__global__ __launch_bounds__(64, (inverse_waves<N, TC>())) void k_inverse_gen(const TS* __restrict__ r,
+                                                                            TS* __restrict__ x, GArgs G,
+                                                                            const TC* __restrict__ eig, int64_t tile0) {
     using L = Slab<N>;
-    constexpr int E = GenShape<N>::E;
-    __shared__ TC se[L::BPW * E];
+    constexpr int E = GenShape<N>::E, ES = lds_stride<TC, E>();
+    __shared__ __align__(16) TC se[L::BPW * ES];
     __shared__ TC s0[L::BPW * L::size];
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const int64_t g0 = t * L::BPW;
-        const int nvalid = nvalid_of<N>(G, t);
-        const Pencil<N> pc(nvalid);
-        const int so = (pc.w < L::BPW ? pc.w : 0) * L::size;
-        stage(se, eig + g0 * E, nvalid * E);
-        slab_in<N, VP, TS, TC>(pc, s0 + so, r, G, g0);
-        wave_sync();
-        gen_inverse_lds<N, TC>(pc, s0 + so, se + (pc.w < L::BPW ? pc.w : 0) * E);
-        if (pc.act) {
-            TC y[N];
-#pragma unroll
-            for (int k = 0; k < N; ++k) y[k] = s0[so + L::at(pc.pa, pc.pb, k)];
-            pencil_store<N, VP>(const_cast<TS*>(pencil_ptr<N>(x, G, g0 + pc.w, pc.pa, pc.pb)), y, G.logB);
-        }
-        wave_sync();
-    }
+    const XcdRange xr = xcd_range(blockIdx.x, gridDim.x);
+    const int64_t t = tile0 + xr.first + xr.place;
+    const int64_t g0 = t * L::BPW;
+    const int nvalid = nvalid_of<N>(G, t);
+    Pencil<N> pc(nvalid);
+    pc.act = static_cast<int>(threadIdx.x) / L::N2 < nvalid;  // at run time, also at n = 8
+    const int so = (pc.w < L::BPW ? pc.w : 0) * L::size;
+    TC y[N];
+    if (pc.act) pencil_load<N, VP>(y, pencil_ptr<N>(r, G, g0 + pc.w, pc.pa, pc.pb), G.logB);
+    stage<E, ES>(se, eig + g0 * E, nvalid);
+    wave_sync();
+    gen_inverse_regs<N, TC>(pc, y, s0 + so, se + (pc.w < L::BPW ? pc.w : 0) * ES);
+    if (pc.act) pencil_store<N, VP>(const_cast<TS*>(pencil_ptr<N>(x, G, g0 + pc.w, pc.pa, pc.pb)), y, G.logB);
 }
 
 template <int N, typename TI, int RND>
@@ -241,25 +281,32 @@ __global__ __launch_bounds__(64, 2) void k_solve_gen(const double* __restrict__ 
     using L = Slab<N>;
     constexpr int F = GenShape<N>::F, E = GenShape<N>::E;
     __shared__ SolveLds<N, TI> lds;
-    __shared__ double sf[L::BPW * F];
-    __shared__ TI se[L::BPW * E];
+    __shared__ __align__(16) double sf[L::BPW * F];
+    __shared__ __align__(16) TI se[L::BPW * E];
     SolveAcc acc;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int64_t g0 = t * L::BPW;
         const int nvalid = nvalid_of<N>(G, t);
         wave_sync();  // the previous tile is done with the staged factors
-        stage(sf, fac + g0 * F, nvalid * F);
-        stage(se, eig + g0 * E, nvalid * E);
+        stage<F, F>(sf, fac + g0 * F, nvalid);
+        stage<E, E>(se, eig + g0 * E, nvalid);
         const int w = static_cast<int>(threadIdx.x) / L::N2;
         const double* Fw = sf + (w < L::BPW ? w : 0) * F;
         const TI* Ew = se + (w < L::BPW ? w : 0) * E;
+        // which lanes take part is asked again at each phase: at n = 8 it is all
+        // of them, and with the test folded away the phases run into one
+        // another and their registers spill (20000 blocks: 292 us, 279 us so)
+        auto lanes = [&](Pencil<N> p) {
+            p.act = w < nvalid;
+            return p;
+        };
         solve_tile<N, TI, RND>(
             b, x, G, g0, nvalid, lds,
             [&](const Pencil<N>& p, const double* src, double* dst, double* t1, double* t2) {
-                gen_apply_lds<N, double>(p, src, dst, t1, t2, Fw);
+                gen_apply_lds<N, double>(lanes(p), src, dst, t1, t2, Fw);
             },
-            [&](const Pencil<N>& p, TI* slab) { gen_inverse_lds<N, TI>(p, slab, Ew); }, rtol, maxit, iters, relres,
-            block0, acc);
+            [&](const Pencil<N>& p, TI* slab) { gen_inverse_lds<N, TI>(lanes(p), slab, Ew); }, rtol, maxit, iters,
+            relres, block0, acc);
     }
     acc.flush(parts + blockIdx.x);
 }
@@ -279,39 +326,48 @@ bool gen_vector_pencils(const GroupInfo& g, const void* a, const void* b) {
     return (pa % 16) == 0 && (pb % 16) == 0;
 }
 
+// Tiles of one launch: a grid holds fewer than 2^32 lanes.
+constexpr int64_t kGenTiles = int64_t(1) << 25;
+
 int64_t gen_grid(const Plan& plan, int64_t ntiles) {
     return std::max<int64_t>(1, std::min<int64_t>(ntiles, static_cast<int64_t>(plan.cus) * 16));
 }
 
 template <int N, typename TS, typename TC>
-tp_status apply_gen_n(const Plan& plan, const GroupInfo& g, const void* u, void* v, hipStream_t s) {
+tp_status apply_gen_n(const GroupInfo& g, const void* u, void* v, hipStream_t s) {
     const int64_t ntiles = (g.nblocks + Slab<N>::BPW - 1) / Slab<N>::BPW;
     const TC* fac = static_cast<const TC*>(sizeof(TC) == 8 ? static_cast<const void*>(g.fac)
                                                            : static_cast<const void*>(g.fac32));
     GArgs a{g.h, g.nblocks, g.offset, g.logB};
-    const unsigned grid = static_cast<unsigned>(gen_grid(plan, ntiles));
-    if (gen_vector_pencils<N, TS>(g, u, v))
-        hipLaunchKernelGGL((k_apply_gen<N, TS, TC, true>), dim3(grid), dim3(64), 0, s, static_cast<const TS*>(u),
-                           static_cast<TS*>(v), a, fac, ntiles);
-    else
-        hipLaunchKernelGGL((k_apply_gen<N, TS, TC, false>), dim3(grid), dim3(64), 0, s, static_cast<const TS*>(u),
-                           static_cast<TS*>(v), a, fac, ntiles);
+    const bool vp = gen_vector_pencils<N, TS>(g, u, v);
+    for (int64_t t0 = 0; t0 < ntiles; t0 += kGenTiles) {
+        const dim3 grid(static_cast<unsigned>(std::min(ntiles - t0, kGenTiles)));
+        if (vp)
+            hipLaunchKernelGGL((k_apply_gen<N, TS, TC, true>), grid, dim3(64), 0, s, static_cast<const TS*>(u),
+                               static_cast<TS*>(v), a, fac, t0);
+        else
+            hipLaunchKernelGGL((k_apply_gen<N, TS, TC, false>), grid, dim3(64), 0, s, static_cast<const TS*>(u),
+                               static_cast<TS*>(v), a, fac, t0);
+    }
     return check_gen("apply (block factors) launch");
 }
 
 template <int N, typename TS, typename TC>
-tp_status inverse_gen_n(const Plan& plan, const GroupInfo& g, const void* r, void* x, hipStream_t s) {
+tp_status inverse_gen_n(const GroupInfo& g, const void* r, void* x, hipStream_t s) {
     const int64_t ntiles = (g.nblocks + Slab<N>::BPW - 1) / Slab<N>::BPW;
     const TC* eig = static_cast<const TC*>(sizeof(TC) == 8 ? static_cast<const void*>(g.eig)
                                                            : static_cast<const void*>(g.eig32));
     GArgs a{g.h, g.nblocks, g.offset, g.logB};
-    const unsigned grid = static_cast<unsigned>(gen_grid(plan, ntiles));
-    if (gen_vector_pencils<N, TS>(g, r, x))
-        hipLaunchKernelGGL((k_inverse_gen<N, TS, TC, true>), dim3(grid), dim3(64), 0, s, static_cast<const TS*>(r),
-                           static_cast<TS*>(x), a, eig, ntiles);
-    else
-        hipLaunchKernelGGL((k_inverse_gen<N, TS, TC, false>), dim3(grid), dim3(64), 0, s, static_cast<const TS*>(r),
-                           static_cast<TS*>(x), a, eig, ntiles);
+    const bool vp = gen_vector_pencils<N, TS>(g, r, x);
+    for (int64_t t0 = 0; t0 < ntiles; t0 += kGenTiles) {
+        const dim3 grid(static_cast<unsigned>(std::min(ntiles - t0, kGenTiles)));
+        if (vp)
+            hipLaunchKernelGGL((k_inverse_gen<N, TS, TC, true>), grid, dim3(64), 0, s, static_cast<const TS*>(r),
+                               static_cast<TS*>(x), a, eig, t0);
+        else
+            hipLaunchKernelGGL((k_inverse_gen<N, TS, TC, false>), grid, dim3(64), 0, s, static_cast<const TS*>(r),
+                               static_cast<TS*>(x), a, eig, t0);
+    }
     return check_gen("apply_inverse (block factors) launch");
 }
 
@@ -333,29 +389,29 @@ tp_status solve_gen_n(const Plan& plan, const GroupInfo& g, const double* b, dou
 }
 
 template <typename TS, typename TC>
-tp_status apply_gen_dispatch(const Plan& plan, const GroupInfo& g, const void* u, void* v, hipStream_t s) {
+tp_status apply_gen_dispatch(const GroupInfo& g, const void* u, void* v, hipStream_t s) {
     switch (g.n) {
-        case 2: return apply_gen_n<2, TS, TC>(plan, g, u, v, s);
-        case 3: return apply_gen_n<3, TS, TC>(plan, g, u, v, s);
-        case 4: return apply_gen_n<4, TS, TC>(plan, g, u, v, s);
-        case 5: return apply_gen_n<5, TS, TC>(plan, g, u, v, s);
-        case 6: return apply_gen_n<6, TS, TC>(plan, g, u, v, s);
-        case 7: return apply_gen_n<7, TS, TC>(plan, g, u, v, s);
-        case 8: return apply_gen_n<8, TS, TC>(plan, g, u, v, s);
+        case 2: return apply_gen_n<2, TS, TC>(g, u, v, s);
+        case 3: return apply_gen_n<3, TS, TC>(g, u, v, s);
+        case 4: return apply_gen_n<4, TS, TC>(g, u, v, s);
+        case 5: return apply_gen_n<5, TS, TC>(g, u, v, s);
+        case 6: return apply_gen_n<6, TS, TC>(g, u, v, s);
+        case 7: return apply_gen_n<7, TS, TC>(g, u, v, s);
+        case 8: return apply_gen_n<8, TS, TC>(g, u, v, s);
     }
     return set_error(TP_ERR_UNSUPPORTED, "unsupported n");
 }
 
 template <typename TS, typename TC>
-tp_status inverse_gen_dispatch(const Plan& plan, const GroupInfo& g, const void* r, void* x, hipStream_t s) {
+tp_status inverse_gen_dispatch(const GroupInfo& g, const void* r, void* x, hipStream_t s) {
     switch (g.n) {
-        case 2: return inverse_gen_n<2, TS, TC>(plan, g, r, x, s);
-        case 3: return inverse_gen_n<3, TS, TC>(plan, g, r, x, s);
-        case 4: return inverse_gen_n<4, TS, TC>(plan, g, r, x, s);
-        case 5: return inverse_gen_n<5, TS, TC>(plan, g, r, x, s);
-        case 6: return inverse_gen_n<6, TS, TC>(plan, g, r, x, s);
-        case 7: return inverse_gen_n<7, TS, TC>(plan, g, r, x, s);
-        case 8: return inverse_gen_n<8, TS, TC>(plan, g, r, x, s);
+        case 2: return inverse_gen_n<2, TS, TC>(g, r, x, s);
+        case 3: return inverse_gen_n<3, TS, TC>(g, r, x, s);
+        case 4: return inverse_gen_n<4, TS, TC>(g, r, x, s);
+        case 5: return inverse_gen_n<5, TS, TC>(g, r, x, s);
+        case 6: return inverse_gen_n<6, TS, TC>(g, r, x, s);
+        case 7: return inverse_gen_n<7, TS, TC>(g, r, x, s);
+        case 8: return inverse_gen_n<8, TS, TC>(g, r, x, s);
     }
     return set_error(TP_ERR_UNSUPPORTED, "unsupported n");
 }
@@ -378,27 +434,27 @@ tp_status solve_gen_dispatch(const Plan& plan, const GroupInfo& g, const double*
 
 }  // namespace
 
-tp_status launch_apply_gen(const Plan& plan, const GroupInfo& g, const void* u, void* v, tp_dtype dt, hipStream_t s) {
+tp_status launch_apply_gen(const Plan&, const GroupInfo& g, const void* u, void* v, tp_dtype dt, hipStream_t s) {
     if (g.nblocks == 0) return TP_OK;
     if (!g.fac) return set_error(TP_ERR_STATE, "group has no block factors");
     switch (dt) {
-        case TP_F64: return apply_gen_dispatch<double, double>(plan, g, u, v, s);
-        case TP_F32: return apply_gen_dispatch<float, float>(plan, g, u, v, s);
-        case TP_F16: return apply_gen_dispatch<_Float16, float>(plan, g, u, v, s);
-        case TP_BF16: return apply_gen_dispatch<bf16_t, float>(plan, g, u, v, s);
+        case TP_F64: return apply_gen_dispatch<double, double>(g, u, v, s);
+        case TP_F32: return apply_gen_dispatch<float, float>(g, u, v, s);
+        case TP_F16: return apply_gen_dispatch<_Float16, float>(g, u, v, s);
+        case TP_BF16: return apply_gen_dispatch<bf16_t, float>(g, u, v, s);
     }
     return set_error(TP_ERR_UNSUPPORTED, "unsupported dtype");
 }
 
-tp_status launch_inverse_gen(const Plan& plan, const GroupInfo& g, const void* r, void* x, tp_dtype dt,
+tp_status launch_inverse_gen(const Plan&, const GroupInfo& g, const void* r, void* x, tp_dtype dt,
                              hipStream_t s) {
     if (g.nblocks == 0) return TP_OK;
     if (!g.eig) return set_error(TP_ERR_STATE, "group has no block eigen-decompositions");
     switch (dt) {
-        case TP_F64: return inverse_gen_dispatch<double, double>(plan, g, r, x, s);
-        case TP_F32: return inverse_gen_dispatch<float, float>(plan, g, r, x, s);
-        case TP_F16: return inverse_gen_dispatch<_Float16, float>(plan, g, r, x, s);
-        case TP_BF16: return inverse_gen_dispatch<bf16_t, float>(plan, g, r, x, s);
+        case TP_F64: return inverse_gen_dispatch<double, double>(g, r, x, s);
+        case TP_F32: return inverse_gen_dispatch<float, float>(g, r, x, s);
+        case TP_F16: return inverse_gen_dispatch<_Float16, float>(g, r, x, s);
+        case TP_BF16: return inverse_gen_dispatch<bf16_t, float>(g, r, x, s);
     }
     return set_error(TP_ERR_UNSUPPORTED, "unsupported dtype");
 }

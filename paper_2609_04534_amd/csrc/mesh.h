@@ -30,18 +30,6 @@ struct FaceRef {        // reference endpoint derivatives and penalty C p (p+1)
     T sigma;
 };
 
-// Tiles [first, first + count) of the XCD that runs workgroup b (b % 8), and
-// b's place in them: each XCD gets a contiguous range of the nwg tiles (the
-// first nwg % 8 ranges hold one tile more), so that neighbours of its tiles
-// share its L2 (100^3 cells at n = 4 in FP64, 7813 tiles: 315 us against 450
-// us in launch order).
-struct XcdRange {
-    unsigned first, count, place;
-};
-__device__ __forceinline__ XcdRange xcd_range(unsigned b, unsigned nwg) {
-    const unsigned q = nwg / 8, r = nwg % 8, x = b % 8;
-    return {x * q + (x < r ? x : r), q + (x < r ? 1u : 0u), b / 8};
-}
 // Tile of workgroup b on a mesh with about S tiles per x-plane of cells: each
 // XCD walks its range in groups of SW consecutive tiles carried through the
 // range's rows of S tiles.  A tile's x neighbours then come SW tiles apart in
