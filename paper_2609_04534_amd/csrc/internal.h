@@ -261,6 +261,12 @@ tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, const vo
 // FP64 storage.
 int mg_storage(const tp_mg* m);
 const float* mg_result32(const tp_mg* m);
+// The V-cycle of a CG iteration, z = V(r), with *count partials of (r, z) in
+// part (at most one per 64 cells for n <= 4, one per cell above).  With FP32
+// level storage the caller has put r into mg_rhs32 and z stays in mg_result32.
+float* mg_rhs32(const tp_mg* m);
+tp_status mg_enqueue_iteration(const tp_mg* m, const double* r, double* z, double* part, int64_t* count, const void* st,
+                               bool f32, hipStream_t s);
 tp_status mg_enqueue_widen(const tp_mg* m, double* dst, hipStream_t s);
 // Partial (a, b) per 64-cell tile with b in FP64 or (b32) FP32.
 tp_status mg_enqueue_dot(const tp_mg* m, const double* a, const void* b, bool b32, double* part, const void* st,

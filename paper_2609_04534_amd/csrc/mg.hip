@@ -103,10 +103,13 @@ __global__ __launch_bounds__(64 * N, 4) void k_mg_jacobi0(const TS* __restrict__
 // workgroup's cells, A u_in from the cells and their six neighbours, the block
 // inverse (E holds omega) in precision TI on the residual planes.  u_out must
 // not alias u_in (other workgroups still read u_in).
-template <int N, typename TI, bool HERM, typename TS, int W = 1>
+// DOT: also a partial of (r, u_out) per workgroup, for CG: r is read once more
+// here (64^3 cells, n = 4, FP64: 116 -> 132 us), where a kernel of its own read
+// both vectors (46 us).
+template <int N, typename TI, bool HERM, typename TS, int W = 1, bool DOT = false>
 __global__ __launch_bounds__(64 * N, (tile_waves<N, MgTC<TS>, W>())) void k_mg_smooth(
     const TS* __restrict__ b, const TS* __restrict__ uin, TS* __restrict__ uout, MeshArgs G, TileTab<N, MgTC<TS>, HERM> R,
-    TileInv<N, TI> E, const PcgState* __restrict__ st) {
+    TileInv<N, TI> E, const PcgState* __restrict__ st, const double* __restrict__ r, double* __restrict__ part) {
     using TC = MgTC<TS>;
     if (done_flag(st)) return;
     constexpr int N2 = N * N, N3 = N * N * N;
@@ -126,13 +129,25 @@ __global__ __launch_bounds__(64 * N, (tile_waves<N, MgTC<TS>, W>())) void k_mg_s
     // the planes of the two element types do not coincide
     if constexpr (sizeof(TC) != sizeof(TI)) tile_sync();
     tile_fdm<N, TI, W>(E, T, reinterpret_cast<Cells<TI, W>(*)[64]>(lds), v);
-    if (!T.valid) return;
+    double s = 0.0;
+    if (T.valid) {
 #pragma unroll
-    for (int e = 0; e < N2; ++e) {
-        Cells<double, W> uv = ld_cells<double, W>(uin + base + (e << 6));
+        for (int e = 0; e < N2; ++e) {
+            Cells<double, W> uv = ld_cells<double, W>(uin + base + (e << 6));
 #pragma unroll
-        for (int k = 0; k < W; ++k) uv.v[k] += static_cast<double>(v[e].v[k]);
-        st_cells<false>(uout + base + (e << 6), uv);
+            for (int k = 0; k < W; ++k) uv.v[k] += static_cast<double>(v[e].v[k]);
+            st_cells<false>(uout + base + (e << 6), uv);
+            if constexpr (DOT) {
+                const Cells<double, W> rv = ld_cells<double, W>(r + base + (e << 6));
+#pragma unroll
+                for (int k = 0; k < W; ++k) s = fma(rv.v[k], static_cast<double>(static_cast<TS>(uv.v[k])), s);
+            }
+        }
+    }
+    if constexpr (DOT) {
+        tile_sync();
+        s = tile_sum<N>(s, reinterpret_cast<double*>(lds));
+        if (threadIdx.x == 0 && threadIdx.y == 0) part[blockIdx.x] = s;
     }
 }
 
@@ -581,12 +596,13 @@ __global__ __launch_bounds__(64, 2) void k_mg_jacobi0_wave(const TS* __restrict_
 // One Chebyshev update u_out = u_in + omega D^{-1} (b - A u_in) of the
 // wave's cell: the operator row by x-pencils, the residual into the slab in
 // precision TI, the block inverse, the update by z-pencils.
-template <int N, typename TI, bool VP, typename T = double>
+template <int N, typename TI, bool VP, typename T = double, bool DOT = false>
 __global__ __launch_bounds__(64, 2) void k_mg_smooth_wave(const T* __restrict__ b,
                                                         const T* __restrict__ uin, T* __restrict__ uout,
                                                         MeshArgs G, const T* __restrict__ tab,
                                                         WaveFace<N, T> F, const TI* __restrict__ tabS,
-                                                        double omega, const PcgState* __restrict__ st) {
+                                                        double omega, const PcgState* __restrict__ st,
+                                                        const double* __restrict__ r, double* __restrict__ part) {
     if (done_flag(st)) return;
     using SL = Slab<N>;
     constexpr int TAB = 2 * (EOShape<N>::SE + EOShape<N>::SO);
@@ -632,6 +648,7 @@ __global__ __launch_bounds__(64, 2) void k_mg_smooth_wave(const T* __restrict__ 
     wave_sync();
     double d[N];
     wave_block_inverse<N, TI>(pc, slab, stab, stab + TABM, G, d);
+    double s = 0.0;
     if (pc.act) {
         const int64_t pb = zpencil_base<N>(G, c, pc);
         double uv[N];
@@ -644,6 +661,16 @@ __global__ __launch_bounds__(64, 2) void k_mg_smooth_wave(const T* __restrict__ 
 #pragma unroll
         for (int k = 0; k < N; ++k) uv[k] = fma(omega, d[k], uv[k]);
         pencil_store<N, VP>(uout + pb, uv, G.logB);
+        if constexpr (DOT) {
+            double rv[N];
+            pencil_load<N, VP>(rv, r + pb, G.logB);
+#pragma unroll
+            for (int k = 0; k < N; ++k) s = fma(rv[k], static_cast<double>(static_cast<T>(uv[k])), s);
+        }
+    }
+    if constexpr (DOT) {
+        s = wave_sum(s);
+        if (threadIdx.x == 0) part[c] = s;
     }
 }
 
@@ -985,6 +1012,15 @@ struct tp_mg {
 
 namespace {
 
+// Where the finest level's last update leaves the partials of (r, u): count of
+// them in part (0: it did not, as when the finest level has no update of its
+// own).  r in FP64, 16-byte aligned.
+struct RzPartials {
+    const double* r;
+    double* part;
+    int64_t count;
+};
+
 // Embeddings into the children and their transposes.
 template <int N>
 void prolongation_tables(const Plan& plan, ProlTab<N>& P, ProlTab<N>& PT) {
@@ -995,7 +1031,8 @@ void prolongation_tables(const Plan& plan, ProlTab<N>& P, ProlTab<N>& PT) {
 }
 
 template <int N, typename TI, bool HERM, typename TS>
-tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgState* st, hipStream_t s) {
+tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgState* st, hipStream_t s,
+                       RzPartials* rz = nullptr) {
     const Plan& plan = *m->plan;
     const MgLevel& L = m->lv[l];
     TS* Lt = static_cast<TS*>(L.t);
@@ -1033,12 +1070,27 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
         if constexpr (sizeof(TS) == 8) {
             if (pairs) {
                 hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS, 2>), dim3(tile_grid(L.G, 2)), dim3(64, N), 0, s, b,
-                                   from, to, L.G, R, E[j], st);
+                                   from, to, L.G, R, E[j], st, nullptr, nullptr);
                 return;
             }
         }
         hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS>), dim3(grid), dim3(64, N), 0, s, b, from, to, L.G, R, E[j],
-                           st);
+                           st, nullptr, nullptr);
+    };
+    // the last update, with the partials of (r, u) when they are asked for
+    auto last_step = [&](const TS* from, TS* to, int j) {
+        if (!rz) return step(from, to, j);
+        if constexpr (sizeof(TS) == 8) {
+            if (pairs) {
+                rz->count = tile_grid(L.G, 2);
+                hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS, 2, true>), dim3(tile_grid(L.G, 2)), dim3(64, N), 0, s,
+                                   b, from, to, L.G, R, E[j], st, rz->r, rz->part);
+                return;
+            }
+        }
+        rz->count = grid;
+        hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS, 1, true>), dim3(grid), dim3(64, N), 0, s, b, from, to, L.G, R,
+                           E[j], st, rz->r, rz->part);
     };
     hipLaunchKernelGGL((k_mg_jacobi0<N, TI, TS>), dim3(grid), dim3(64, N), 0, s, b, u, L.G, E[0], st);
     step(u, Lt, 1);
@@ -1064,7 +1116,7 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
     hipLaunchKernelGGL((k_mg_prolong<N, TS>), dim3(grid), dim3(64, N), 0, s, Cu, u, Lt, L.G, C.G, P, st);
     step(Lt, u, 0);
     step(u, Lt, 1);
-    step(Lt, u, 2);
+    last_step(Lt, u, 2);
     return check_launch("smoothing");
 }
 
@@ -1072,8 +1124,8 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
 // move as 16-byte vectors where VP), level vectors and operator rows in TS
 // (FP64, or FP32 for the FP32-storage hierarchy).
 template <int N, typename TI, bool VP, typename TS>
-tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgState* st,
-                            hipStream_t s) {
+tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgState* st, hipStream_t s,
+                            RzPartials* rz = nullptr) {
     const Plan& plan = *m->plan;
     const MgLevel& L = m->lv[l];
     TS* Lt = static_cast<TS*>(L.t);
@@ -1091,7 +1143,14 @@ tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const 
     prolongation_tables<N>(plan, P, PT);
     auto step = [&](const TS* from, TS* to, int j) {
         hipLaunchKernelGGL((k_mg_smooth_wave<N, TI, VP, TS>), dim3(grid), dim3(64), 0, s, b, from, to, L.G, tabA, F,
-                           tabS, m->omega[j], st);
+                           tabS, m->omega[j], st, nullptr, nullptr);
+    };
+    // the last update, with the partials of (r, u) when they are asked for
+    auto last_step = [&](const TS* from, TS* to, int j) {
+        if (!rz) return step(from, to, j);
+        rz->count = grid;
+        hipLaunchKernelGGL((k_mg_smooth_wave<N, TI, VP, TS, true>), dim3(grid), dim3(64), 0, s, b, from, to, L.G, tabA,
+                           F, tabS, m->omega[j], st, rz->r, rz->part);
     };
     hipLaunchKernelGGL((k_mg_jacobi0_wave<N, TI, VP, TS>), dim3(grid), dim3(64), 0, s, b, u, L.G, tabS, m->omega[0],
                        st);
@@ -1112,7 +1171,7 @@ tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const 
         if (stt != TP_OK) return stt;
         step(Lt, u, 0);
         step(u, Lt, 1);
-        step(Lt, u, 2);
+        last_step(Lt, u, 2);
         return check_launch("smoothing");
     }
     const MgLevel& C = m->lv[l + 1];
@@ -1127,18 +1186,19 @@ tp_status vcycle_level_wave(const tp_mg* m, size_t l, const TS* b, TS* u, const 
     hipLaunchKernelGGL((k_mg_prolong_wave<N, VP, TS>), dim3(grid), dim3(64), 0, s, Cu, u, Lt, L.G, C.G, P, st);
     step(Lt, u, 0);
     step(u, Lt, 1);
-    step(Lt, u, 2);
+    last_step(Lt, u, 2);
     return check_launch("smoothing");
 }
 
 template <typename TI, typename TS>
-tp_status vcycle_dispatch(const tp_mg* m, const TS* b, TS* u, const PcgState* st, hipStream_t s) {
+tp_status vcycle_dispatch(const tp_mg* m, const TS* b, TS* u, const PcgState* st, hipStream_t s,
+                          RzPartials* rz) {
     switch (m->n) {
-        case 2: return vcycle_level<2, TI, false, TS>(m, 0, b, u, st, s);
-        case 3: return vcycle_level<3, TI, false, TS>(m, 0, b, u, st, s);
+        case 2: return vcycle_level<2, TI, false, TS>(m, 0, b, u, st, s, rz);
+        case 3: return vcycle_level<3, TI, false, TS>(m, 0, b, u, st, s, rz);
         case 4:
-            return m->plan->basis == TP_BASIS_HERMITE ? vcycle_level<4, TI, true, TS>(m, 0, b, u, st, s)
-                                                      : vcycle_level<4, TI, false, TS>(m, 0, b, u, st, s);
+            return m->plan->basis == TP_BASIS_HERMITE ? vcycle_level<4, TI, true, TS>(m, 0, b, u, st, s, rz)
+                                                      : vcycle_level<4, TI, false, TS>(m, 0, b, u, st, s, rz);
         default: break;
     }
     {
@@ -1148,12 +1208,12 @@ tp_status vcycle_dispatch(const tp_mg* m, const TS* b, TS* u, const PcgState* st
         const bool vp = reinterpret_cast<uintptr_t>(b) % 16 == 0 && reinterpret_cast<uintptr_t>(u) % 16 == 0;
         constexpr bool v6 = (6 * sizeof(TS)) % 16 == 0;
         switch (m->n) {
-            case 5: return vcycle_level_wave<5, TI, false, TS>(m, 0, b, u, st, s);
-            case 6: return vp && v6 ? vcycle_level_wave<6, TI, v6, TS>(m, 0, b, u, st, s)
-                                    : vcycle_level_wave<6, TI, false, TS>(m, 0, b, u, st, s);
-            case 7: return vcycle_level_wave<7, TI, false, TS>(m, 0, b, u, st, s);
-            case 8: return vp ? vcycle_level_wave<8, TI, true, TS>(m, 0, b, u, st, s)
-                              : vcycle_level_wave<8, TI, false, TS>(m, 0, b, u, st, s);
+            case 5: return vcycle_level_wave<5, TI, false, TS>(m, 0, b, u, st, s, rz);
+            case 6: return vp && v6 ? vcycle_level_wave<6, TI, v6, TS>(m, 0, b, u, st, s, rz)
+                                    : vcycle_level_wave<6, TI, false, TS>(m, 0, b, u, st, s, rz);
+            case 7: return vcycle_level_wave<7, TI, false, TS>(m, 0, b, u, st, s, rz);
+            case 8: return vp ? vcycle_level_wave<8, TI, true, TS>(m, 0, b, u, st, s, rz)
+                              : vcycle_level_wave<8, TI, false, TS>(m, 0, b, u, st, s, rz);
             default: break;
         }
     }
@@ -1310,25 +1370,52 @@ tp_status convert_launch(const void* src, void* dst, bool to_f32, int64_t n, con
 }  // namespace
 
 namespace tpfdm {
-tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, const void* st, bool f32, hipStream_t s) {
+namespace {
+// The cycle on the finest level's vectors: with FP32 level storage its own
+// right-hand side and result.
+tp_status vcycle_on_level(const tp_mg* m, const double* b, double* u, const PcgState* ps, bool f32, hipStream_t s,
+                          RzPartials* rz) {
     // the smoother reads the plan's cell-block eigen tables at every enqueue
     if (m->plan->inverse_op != TP_OP_CELL || m->plan->factor_mode != TP_FACTOR_SCALED)
         return set_error(TP_ERR_STATE, "the plan's inverse setup is no longer TP_OP_CELL, TP_FACTOR_SCALED");
-    const PcgState* ps = static_cast<const PcgState*>(st);
     if (m->storage == TP_F32) {
-        // b into the hierarchy's FP32 right-hand side, the cycle, and (when
-        // u is given) the FP32 result back to FP64
-        const MgLevel& L0 = m->lv[0];
-        tp_status r = convert_launch(b, L0.b, true, L0.elems, ps, s);
-        if (r != TP_OK) return r;
-        const float* b32 = static_cast<const float*>(L0.b);
-        float* u32 = static_cast<float*>(L0.u);
-        r = f32 ? vcycle_dispatch<float, float>(m, b32, u32, ps, s) : vcycle_dispatch<double, float>(m, b32, u32, ps, s);
-        if (r != TP_OK || !u) return r;
-        return convert_launch(u32, u, false, L0.elems, ps, s);
+        const float* b32 = static_cast<const float*>(m->lv[0].b);
+        float* u32 = static_cast<float*>(m->lv[0].u);
+        return f32 ? vcycle_dispatch<float, float>(m, b32, u32, ps, s, rz)
+                   : vcycle_dispatch<double, float>(m, b32, u32, ps, s, rz);
     }
-    return f32 ? vcycle_dispatch<float, double>(m, b, u, ps, s) : vcycle_dispatch<double, double>(m, b, u, ps, s);
+    return f32 ? vcycle_dispatch<float, double>(m, b, u, ps, s, rz)
+               : vcycle_dispatch<double, double>(m, b, u, ps, s, rz);
 }
+}  // namespace
+
+tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, const void* st, bool f32, hipStream_t s) {
+    const PcgState* ps = static_cast<const PcgState*>(st);
+    if (m->storage != TP_F32) return vcycle_on_level(m, b, u, ps, f32, s, nullptr);
+    // b into the hierarchy's FP32 right-hand side, the cycle, and (when u is
+    // given) the FP32 result back to FP64
+    const MgLevel& L0 = m->lv[0];
+    tp_status r = convert_launch(b, L0.b, true, L0.elems, ps, s);
+    if (r == TP_OK) r = vcycle_on_level(m, nullptr, nullptr, ps, f32, s, nullptr);
+    if (r != TP_OK || !u) return r;
+    return convert_launch(L0.u, u, false, L0.elems, ps, s);
+}
+
+tp_status mg_enqueue_iteration(const tp_mg* m, const double* r, double* z, double* part, int64_t* count, const void* st,
+                               bool f32, hipStream_t s) {
+    const PcgState* ps = static_cast<const PcgState*>(st);
+    const bool f32s = m->storage == TP_F32;
+    RzPartials rz{r, part, 0};
+    tp_status e = vcycle_on_level(m, r, z, ps, f32, s, &rz);
+    if (e == TP_OK && rz.count == 0) {
+        rz.count = m->n <= kLaneMaxN ? (m->lv[0].G.ncells + 63) / 64 : m->lv[0].G.ncells;
+        e = mg_enqueue_dot(m, r, f32s ? m->lv[0].u : static_cast<const void*>(z), f32s, part, st, s);
+    }
+    *count = rz.count;
+    return e;
+}
+
+float* mg_rhs32(const tp_mg* m) { return m->storage == TP_F32 ? static_cast<float*>(m->lv[0].b) : nullptr; }
 
 int mg_storage(const tp_mg* m) { return m->storage; }
 

@@ -63,11 +63,13 @@ __global__ __launch_bounds__(64 * N, (tile_waves<N, double, W>())) void k_pcg_aq
 }
 
 // Fixed-order sums of K arrays of count partials (array k starts at part +
-// k count) by one workgroup of kRed threads, returned to every thread.  (By
+// k count; the first array holds only first) by one workgroup of kRed threads,
+// returned to every thread.  (By
 // 256 threads, one array after the other, 13824 partials took 15 us an array.)
 constexpr int kRed = 1024;
 template <int K>
-__device__ __forceinline__ void block_sums(const double* __restrict__ part, int64_t count, double (&out)[K]) {
+__device__ __forceinline__ void block_sums(const double* __restrict__ part, int64_t first, int64_t count,
+                                           double (&out)[K]) {
     __shared__ double red[K][kRed / 64];
     double s[K];
 #pragma unroll
@@ -75,7 +77,7 @@ __device__ __forceinline__ void block_sums(const double* __restrict__ part, int6
 #pragma unroll 4
     for (int64_t i = threadIdx.x; i < count; i += kRed)
 #pragma unroll
-        for (int k = 0; k < K; ++k) s[k] += part[k * count + i];
+        for (int k = 0; k < K; ++k) s[k] += k > 0 || i < first ? part[k * count + i] : 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         s[k] = wave_sum(s[k]);
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(kRed) void k_pcg_reduce_start(const double* __restr
                                                            PcgState* __restrict__ st, double rtol, int maxit,
                                                            int norm) {
     double v[3];
-    block_sums<3>(part, count, v);
+    block_sums<3>(part, count, count, v);
     const double rz = v[0], rr = v[1], bb = v[2];
     if (threadIdx.x == 0) {
         PcgState s;
@@ -121,7 +123,7 @@ __global__ __launch_bounds__(kRed) void k_pcg_reduce_alpha(const double* __restr
                                                            PcgState* __restrict__ st) {
     if (st->done) return;
     double pq[1];
-    block_sums<1>(part, count, pq);
+    block_sums<1>(part, count, count, pq);
     if (threadIdx.x == 0) {
         st->pq = pq[0];
         if (!(pq[0] > 0.0) || !finite(pq[0])) {
@@ -133,11 +135,11 @@ __global__ __launch_bounds__(kRed) void k_pcg_reduce_alpha(const double* __restr
 }
 
 // 4.  beta, the iteration count and the convergence test.
-__global__ __launch_bounds__(kRed) void k_pcg_reduce_beta(const double* __restrict__ part, int64_t count,
+__global__ __launch_bounds__(kRed) void k_pcg_reduce_beta(const double* __restrict__ part, int64_t first, int64_t count,
                                                           PcgState* __restrict__ st) {
     if (st->done) return;
     double v[2];
-    block_sums<2>(part, count, v);
+    block_sums<2>(part, first, count, v);
     const double rz = v[0], rr = v[1];
     if (threadIdx.x == 0) {
         const double rz_old = st->rz;
@@ -301,12 +303,12 @@ __global__ __launch_bounds__(64) void k_pcg_start_res(const double* __restrict__
     }
 }
 
-// x += alpha p, r -= alpha q; partial (r, r).
-template <int N, int LB>
+// x += alpha p, r -= alpha q, R32: and r in FP32 to r32; partial (r, r).
+template <int N, int LB, bool R32>
 __global__ __launch_bounds__(64) void k_pcg_axpy(double* __restrict__ x, double* __restrict__ r,
                                                  const double* __restrict__ p, const double* __restrict__ q,
                                                  MeshArgs G, const PcgState* __restrict__ st,
-                                                 double* __restrict__ part, int64_t count) {
+                                                 double* __restrict__ part, int64_t count, float* __restrict__ r32) {
     if (st->done) return;
     constexpr int N3 = N * N * N;
     const double alpha = st->alpha;
@@ -321,6 +323,7 @@ __global__ __launch_bounds__(64) void k_pcg_axpy(double* __restrict__ x, double*
             x[o] = fma(alpha, p[o], x[o]);
             const double rv = fma(-alpha, q[o], r[o]);
             r[o] = rv;
+            if constexpr (R32) r32[o] = static_cast<float>(rv);
             rr = fma(rv, rv, rr);
         }
     }
@@ -572,11 +575,11 @@ __global__ __launch_bounds__(64) void k_pcg_start_res_wave(const double* __restr
     }
 }
 
-template <int N, bool VP>
+template <int N, bool VP, bool R32>
 __global__ __launch_bounds__(64) void k_pcg_axpy_wave(double* __restrict__ x, double* __restrict__ r,
                                                       const double* __restrict__ p, const double* __restrict__ q,
                                                       MeshArgs G, const PcgState* __restrict__ st,
-                                                      double* __restrict__ part, int64_t count) {
+                                                      double* __restrict__ part, int64_t count, float* __restrict__ r32) {
     if (st->done) return;
     const double alpha = st->alpha;
     const int64_t c = blockIdx.x;
@@ -599,6 +602,7 @@ __global__ __launch_bounds__(64) void k_pcg_axpy_wave(double* __restrict__ x, do
         }
         pencil_store<N, VP>(x + pb, xv, lb);
         pencil_store<N, VP>(r + pb, rv, lb);
+        if constexpr (R32) pencil_store<N, VP && N % 4 == 0>(r32 + pb, rv, lb);
     }
     rr = wave_sum(rr);
     if (threadIdx.x == 0) part[count + c] = rr;
@@ -785,30 +789,25 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                     hipLaunchKernelGGL((k_pcg_aq_wave<N, false, false>), dim3(nwg), dim3(64), 0, cs, s->p, s->q, G,
                                        tabA, F, s->st, s->part);
                 hipLaunchKernelGGL(k_pcg_reduce_alpha, dim3(1), dim3(kRed), 0, cs, s->part, aqcnt, s->st);
+                int64_t rzcnt = cnt;   // partials of (r, z)
                 if (s->mg) {
-                    if constexpr (!kLane) {
-                        if (vp)
-                            hipLaunchKernelGGL((k_pcg_axpy_wave<N, true>), dim3(nwg), dim3(64), 0, cs, s->xw, s->r,
-                                               s->p, s->q, G, s->st, s->part, cnt);
+                    // with FP32 level storage the update also writes the cycle's right-hand side
+                    float* r32 = mg_rhs32(s->mg);
+                    auto axpy = [&](auto Rc) {
+                        constexpr bool R32 = decltype(Rc)::value;
+                        if constexpr (kLane)
+                            hipLaunchKernelGGL((k_pcg_axpy<N, LB, R32>), dim3(nwg), dim3(64), 0, cs, s->xw, s->r, s->p,
+                                               s->q, G, s->st, s->part, cnt, r32);
+                        else if (vp)
+                            hipLaunchKernelGGL((k_pcg_axpy_wave<N, true, R32>), dim3(nwg), dim3(64), 0, cs, s->xw,
+                                               s->r, s->p, s->q, G, s->st, s->part, cnt, r32);
                         else
-                            hipLaunchKernelGGL((k_pcg_axpy_wave<N, false>), dim3(nwg), dim3(64), 0, cs, s->xw, s->r,
-                                               s->p, s->q, G, s->st, s->part, cnt);
-                        const bool z32 = mg_storage(s->mg) == TP_F32;
-                        (void)mg_enqueue_vcycle(s->mg, s->r, z32 ? nullptr : s->z, s->st, f32, cs);
-                        (void)mg_enqueue_dot(s->mg, s->r,
-                                             z32 ? static_cast<const void*>(mg_result32(s->mg))
-                                                 : static_cast<const void*>(s->z),
-                                             z32, s->part, s->st, cs);
-                    } else {
-                        hipLaunchKernelGGL((k_pcg_axpy<N, LB>), dim3(nwg), dim3(64), 0, cs, s->xw, s->r, s->p, s->q,
-                                           G, s->st, s->part, cnt);
-                        const bool z32 = mg_storage(s->mg) == TP_F32;
-                        (void)mg_enqueue_vcycle(s->mg, s->r, z32 ? nullptr : s->z, s->st, f32, cs);
-                        (void)mg_enqueue_dot(s->mg, s->r,
-                                             z32 ? static_cast<const void*>(mg_result32(s->mg))
-                                                 : static_cast<const void*>(s->z),
-                                             z32, s->part, s->st, cs);
-                    }
+                            hipLaunchKernelGGL((k_pcg_axpy_wave<N, false, R32>), dim3(nwg), dim3(64), 0, cs, s->xw,
+                                               s->r, s->p, s->q, G, s->st, s->part, cnt, r32);
+                    };
+                    if (r32) axpy(std::true_type{});
+                    else axpy(std::false_type{});
+                    (void)mg_enqueue_iteration(s->mg, s->r, s->z, s->part, &rzcnt, s->st, f32, cs);
                 } else if constexpr (kLane)
                     hipLaunchKernelGGL((k_pcg_update<N, TI, LB>), dim3(nwg), dim3(64), 0, cs, s->xw, s->r, s->z,
                                        s->p, s->q, G, E, s->st, s->part, cnt);
@@ -825,7 +824,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                 else
                     hipLaunchKernelGGL((k_pcg_update_wave<N, TI, false, false>), dim3(nwg), dim3(64), 0, cs, s->xw,
                                        s->r, s->z, s->p, s->q, G, tabS, s->st, s->part, cnt);
-                hipLaunchKernelGGL(k_pcg_reduce_beta, dim3(1), dim3(kRed), 0, cs, s->part, cnt, s->st);
+                hipLaunchKernelGGL(k_pcg_reduce_beta, dim3(1), dim3(kRed), 0, cs, s->part, rzcnt, cnt, s->st);
                 if (s->mg && mg_storage(s->mg) == TP_F32)
                     hipLaunchKernelGGL(k_pcg_dir<float>, dim3(dgrid), dim3(256), 0, cs, mg_result32(s->mg), s->p,
                                        s->elems, s->st);
