@@ -97,36 +97,22 @@ __device__ __forceinline__ void seg_apply_wave(const TS* __restrict__ u, TS* __r
                                                const TC* __restrict__ tab, TC* s1, TC* s2, TC* stab, int64_t t0,
                                                int64_t t1) {
     using L = Slab<N>;
+    ApplyTab<N, TC> A;
+    table_to_regs(A.v, tab, stab, ApplyTab<N, TC>::COUNT);
     const GArgs G = seg_args(sg);
     const int lane = threadIdx.x;
     const int lw = lane / L::N2;
     const int lp = lane - lw * L::N2;
     const int li = lp / N, lj = lp - (lp / N) * N;
     const int so = (lw < L::BPW ? lw : 0) * L::size;
-    // the first tile's loads are in flight while the table is staged
-    constexpr bool kOne = L::BPW == 1;
-    auto load = [&](int64_t t, TC(&x)[N]) {
-        if (lw < L::BPW && lw < nvalid_of<N>(G, t))
-            pencil_load<N, VP>(x, pencil_ptr<N>(u, G, t * L::BPW + lw, li, lj), G.logB);
-    };
-    TC pre[N];
-    if (t0 < t1) load(t0, pre);
-    double len = kOne && t0 < t1 ? wave_lengths(G.h, t0) : 0.0;
-    ApplyTab<N, TC> A;
-    table_to_regs(A.v, tab, stab, ApplyTab<N, TC>::COUNT);
     for (int64_t t = t0; t < t1; ++t) {
         const int64_t g0 = t * L::BPW;
-        const Pencil<N> pc(nvalid_of<N>(G, t));
+        const int nvalid = nvalid_of<N>(G, t);
+        const Pencil<N> pc(nvalid);
         TC x[N];
-#pragma unroll
-        for (int k = 0; k < N; ++k) x[k] = pre[k];
-        const double cur = len;
-        if (t + 1 < t1) {
-            load(t + 1, pre);
-            if (kOne) len = wave_lengths(G.h, t + 1);
-        }
+        if (lw < L::BPW && lw < nvalid) pencil_load<N, VP>(x, pencil_ptr<N>(u, G, g0 + lw, li, lj), G.logB);
         TC sx = TC(1), sy = TC(1), sz = TC(1);
-        if constexpr (kOne) wave_scales(cur, sx, sy, sz);
+        if constexpr (L::BPW == 1) wave_scales(wave_lengths(G.h, g0), sx, sy, sz);
         else if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
         eo_apply_body<N>(pc, x, v, G, g0, s1 + so, s2 + so, A.ME(), A.MO(), A.PE(), A.PO(), sx, sy, sz);
     }
@@ -187,36 +173,23 @@ __device__ __forceinline__ void seg_inverse_wave(const TS* __restrict__ r, TS* _
                                                  int64_t t1) {
     using L = Slab<N>;
     using S = EOShape<N>;
+    InvTab<N, TC> I;
+    table_to_regs(I.v, tab, stab, S::SE + S::SO + N);
+    const TC* lam = stab + S::SE + S::SO;
     const GArgs G = seg_args(sg);
     const int lane = threadIdx.x;
     const int lw = lane / L::N2;
     const int lp = lane - lw * L::N2;
     const int li = lp / N, lj = lp - (lp / N) * N;
     const int so = (lw < L::BPW ? lw : 0) * L::size;
-    constexpr bool kOne = L::BPW == 1;
-    auto load = [&](int64_t t, TC(&y)[N]) {
-        if (lw < L::BPW && lw < nvalid_of<N>(G, t))
-            pencil_load<N, VP>(y, pencil_ptr<N>(r, G, t * L::BPW + lw, li, lj), G.logB);
-    };
-    TC pre[N];
-    if (t0 < t1) load(t0, pre);
-    double len = kOne && t0 < t1 ? wave_lengths(G.h, t0) : 0.0;
-    InvTab<N, TC> I;
-    table_to_regs(I.v, tab, stab, S::SE + S::SO + N);
-    const TC* lam = stab + S::SE + S::SO;
     for (int64_t t = t0; t < t1; ++t) {
         const int64_t g0 = t * L::BPW;
-        const Pencil<N> pc(nvalid_of<N>(G, t));
+        const int nvalid = nvalid_of<N>(G, t);
+        const Pencil<N> pc(nvalid);
         TC xin[N];
-#pragma unroll
-        for (int k = 0; k < N; ++k) xin[k] = pre[k];
-        const double cur = len;
-        if (t + 1 < t1) {
-            load(t + 1, pre);
-            if (kOne) len = wave_lengths(G.h, t + 1);
-        }
+        if (lw < L::BPW && lw < nvalid) pencil_load<N, VP>(xin, pencil_ptr<N>(r, G, g0 + lw, li, lj), G.logB);
         TC sx = TC(1), sy = TC(1), sz = TC(1);
-        if constexpr (kOne) wave_scales(cur, sx, sy, sz);
+        if constexpr (L::BPW == 1) wave_scales(wave_lengths(G.h, g0), sx, sy, sz);
         else if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
         eo_inverse_body<N, VP>(pc, xin, x, G, g0, s1 + so, I.SE(), I.SO(), lam, sx, sy, sz);
     }
@@ -269,10 +242,8 @@ __device__ __forceinline__ void seg_solve(const double* b, double* x, const PSeg
 // Segment of work item w: segments in launch order, each covering the items
 // [first_item, first_item + ceil(tiles / tpw)) of the launch.
 __device__ __forceinline__ int flat_segment(const PSeg* __restrict__ segs, int nseg, int64_t w) {
-    // (counted without an early exit: the starts are loaded together)
     int si = 0;
-#pragma unroll 4
-    for (int i = 1; i < nseg; ++i) si += segs[i].first_item <= w ? 1 : 0;
+    while (si + 1 < nseg && segs[si + 1].first_item <= w) ++si;
     return si;
 }
 
