@@ -153,11 +153,11 @@ __global__ __launch_bounds__(64, 2) void k_inverse_eo(const TS* __restrict__ r, 
     }
 }
 
-// Minimum resident waves per SIMD the solve kernel is compiled for.  FP64
-// inner inverse: n <= 6 fits 128 VGPRs (four waves); at n = 7 that spills,
-// and at n = 8 three waves with more registers measured faster (125 vs
-// 144 us on 32768 blocks) than four.  The FP32 inner one measured faster at
-// 165 VGPRs (n = 8) than squeezed into 128.
+// Minimum resident waves per SIMD the solve kernel is compiled for: four with
+// the FP64 inner inverse up to n = 6.  At n = 7 and 8 the bound is loose: the
+// kernel takes 117 to 123 VGPRs with 16-byte pencils (four waves) and 137 to
+// 142 without them at n = 8 (three).  32768 blocks of n = 8 with the FP32 inner
+// inverse: 177 us when it took 165, 146 us now.
 template <int N, typename TI>
 constexpr int solve_min_waves() {
     return sizeof(TI) == 8 ? (N >= 7 ? 3 : 4) : 2;
