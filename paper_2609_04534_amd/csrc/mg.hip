@@ -914,14 +914,17 @@ DegTab<N> deg_table() {
 }
 
 // dst = src converted element by element (the finest level's right-hand
-// side into the FP32-storage hierarchy, its result back to FP64).
+// side into the FP32-storage hierarchy, its result back to FP64).  Elements
+// [full, n) are a ragged last tile, of which the `rest` first lanes of mask + 1
+// hold cells: the caller's padding lanes are not written.
 template <typename TD, typename TSRC>
 __global__ __launch_bounds__(256) void k_mg_convert(const TSRC* __restrict__ src, TD* __restrict__ dst, int64_t n,
+                                                    int64_t full, int mask, int rest,
                                                     const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * 256)
-        dst[i] = static_cast<TD>(src[i]);
+        if (i < full || (static_cast<int>(i) & mask) < rest) dst[i] = static_cast<TD>(src[i]);
 }
 
 tp_status check_launch(const char* what) {
@@ -1357,14 +1360,18 @@ void launch_dot_wave(const MgLevel& L, const double* a, const void* b, bool b32,
                            L.G, part, ps);
 }
 
-tp_status convert_launch(const void* src, void* dst, bool to_f32, int64_t n, const PcgState* st, hipStream_t s) {
+tp_status convert_launch(const void* src, void* dst, bool to_f32, const tp_mg* m, const PcgState* st, hipStream_t s) {
+    const MgLevel& L = m->lv[0];
+    const int64_t n = L.elems, n3 = int64_t(m->n) * m->n * m->n;
+    const int64_t full = (L.G.ncells >> L.G.logB) * n3 << L.G.logB;
+    const int mask = (1 << L.G.logB) - 1, rest = static_cast<int>(L.G.ncells) & mask;
     const unsigned grid = static_cast<unsigned>(std::min<int64_t>((n + 255) / 256, 8192));
     if (to_f32)
         hipLaunchKernelGGL((k_mg_convert<float, double>), dim3(grid), dim3(256), 0, s, static_cast<const double*>(src),
-                           static_cast<float*>(dst), n, st);
+                           static_cast<float*>(dst), n, full, mask, rest, st);
     else
         hipLaunchKernelGGL((k_mg_convert<double, float>), dim3(grid), dim3(256), 0, s, static_cast<const float*>(src),
-                           static_cast<double*>(dst), n, st);
+                           static_cast<double*>(dst), n, full, mask, rest, st);
     return check_launch("multigrid conversion");
 }
 
@@ -1396,10 +1403,10 @@ tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, const vo
     // b into the hierarchy's FP32 right-hand side, the cycle, and (when u is
     // given) the FP32 result back to FP64
     const MgLevel& L0 = m->lv[0];
-    tp_status r = convert_launch(b, L0.b, true, L0.elems, ps, s);
+    tp_status r = convert_launch(b, L0.b, true, m, ps, s);
     if (r == TP_OK) r = vcycle_on_level(m, nullptr, nullptr, ps, f32, s, nullptr);
     if (r != TP_OK || !u) return r;
-    return convert_launch(L0.u, u, false, L0.elems, ps, s);
+    return convert_launch(L0.u, u, false, m, ps, s);
 }
 
 tp_status mg_enqueue_iteration(const tp_mg* m, const double* r, double* z, double* part, int64_t* count, const void* st,
@@ -1464,7 +1471,7 @@ tp_status mg_enqueue_dot(const tp_mg* m, const double* a, const void* b, bool b3
 
 tp_status mg_enqueue_widen(const tp_mg* m, double* dst, hipStream_t s) {
     if (m->storage != TP_F32) return set_error(TP_ERR_STATE, "the multigrid stores its levels in FP64");
-    return convert_launch(m->lv[0].u, dst, false, m->lv[0].elems, nullptr, s);
+    return convert_launch(m->lv[0].u, dst, false, m, nullptr, s);
 }
 
 const tp_plan* mg_plan(const tp_mg* m) { return m->plan; }

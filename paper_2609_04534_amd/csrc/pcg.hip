@@ -915,9 +915,18 @@ tp_status enqueue_state_copy(tp_pcg* s, hipStream_t stream) {
     return TP_OK;
 }
 
+// The iterate into the caller's x: whole tiles, then the cells of a ragged last
+// tile (the caller's padding lanes are not written).
 tp_status enqueue_result_copy(tp_pcg* s, double* x, hipStream_t stream) {
-    hipError_t e = hipMemcpyAsync(x, s->xw, static_cast<size_t>(s->elems) * sizeof(double), hipMemcpyDeviceToDevice,
-                                  stream);
+    const GroupInfo& g = s->plan->groups[0];
+    const size_t row = sizeof(double) << g.logB, n3 = static_cast<size_t>(g.n) * g.n * g.n;
+    const size_t full = static_cast<size_t>(g.nblocks >> g.logB) * n3 << g.logB;
+    const size_t rest = static_cast<size_t>(g.nblocks) & ((size_t(1) << g.logB) - 1);
+    hipError_t e = hipSuccess;
+    if (full > 0) e = hipMemcpyAsync(x, s->xw, full * sizeof(double), hipMemcpyDeviceToDevice, stream);
+    if (e == hipSuccess && rest > 0)
+        e = hipMemcpy2DAsync(x + full, row, s->xw + full, row, rest * sizeof(double), n3, hipMemcpyDeviceToDevice,
+                             stream);
     if (e != hipSuccess) return hip_error(e, "PCG result copy");
     return TP_OK;
 }
