@@ -381,15 +381,17 @@ int32_t tp_plan_group_kernel(const tp_plan* plan, int32_t group, int32_t call, t
  * launches).  tp_pcg_solve: b, x device FP64 vectors in the plan's layout; x is the
  * initial guess unless x_is_zero (then x is overwritten with zero first) and
  * holds the last iterate on return (x is written only at the end).  b = 0
- * with x_is_zero gives x = 0 at once; b = 0 with a non-zero guess cannot meet
- * the relative test and runs to maxit.  Stops when ||r||_2 <= rtol ||b||_2 for
+ * with x_is_zero gives x = 0 without an iteration; b = 0 with a non-zero guess
+ * cannot meet the relative test and runs to maxit.  Stops when ||r||_2 <= rtol ||b||_2 for
  * the recursively updated residual r, or after maxit iterations
  * (TP_ERR_NOT_CONVERGED), or on a breakdown / non-finite value
  * (TP_ERR_NONFINITE).  Every iteration runs on the device without host
  * synchronisation; the host reads the solver state at least once per
  * check_every iterations (<= 0 selects 16), so up to check_every - 1
- * iterations' kernels run after convergence and return at once.  Synchronises the stream before
- * returning; summary (optional) receives the iterations, whether it
+ * iterations' kernels run after convergence and return at once (with a V-cycle,
+ * whose first graph is launched before the state is read, up to four).
+ * Synchronises the stream before returning; summary (optional) receives the
+ * iterations, whether it
  * converged and the final relative residual.  One solve at a time per
  * solver object. */
 typedef struct {

@@ -1,0 +1,65 @@
+"""The host path of the PCG solves on a machine without a GPU: a stand-in for
+the HIP runtime (hip_stub.cpp) counts graph launches, iterations and
+synchronisations, and lets a solve converge after a set number of
+iterations.  Each test runs in a process of its own, in which the stand-in
+is loaded before the library."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes, json, sys, types
+sys.modules["torch"] = types.ModuleType("torch")   # its runtime is the stand-in
+stub = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+stub.stub_set.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_char_p]
+from paper_2609_04534_amd import tpfdm
+class Vec:
+    def __init__(self, n): self.a = (ctypes.c_double * n)()
+    def data_ptr(self): return ctypes.addressof(self.a)
+class Stream: cuda_stream = 0
+def mesh(n, m):
+    plan = tpfdm.Plan.mesh(n, (m, m, m), (1.0 / m,) * 3)
+    plan.setup_inverse(tpfdm.OP_CELL)
+    return plan, Vec(plan.vector_elems), Vec(plan.vector_elems), tpfdm.PCG(plan)
+def counts():
+    return [stub.stub_graph_launches(), stub.stub_iterations(), stub.stub_syncs()]
+out = []
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("hip") / "hip_stub.so")
+    subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "hip_stub.cpp"), "-o", so], check=True)
+
+    def run(body):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + body + "\nprint(json.dumps(out))", so],
+                           cwd=os.path.dirname(HERE), capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout.splitlines()[-1])
+    return run
+
+
+def test_solve_done_at_its_start(stub):
+    """A block-Jacobi solve that its start has finished launches no iterations,
+    whatever check_every is, and neither preconditioner's does at maxit = 0."""
+    out = stub("""
+plan, b, x, cg = mesh(3, 4)
+for k in (1, 16, 256):
+    stub.stub_set(9, 1, b"")
+    cg.solve(b, x, check_every=k, stream=Stream())
+    out.append(counts()[:2])
+mg = tpfdm.MG(plan)
+for m in (None, mg):
+    cg.set_multigrid(m)
+    stub.stub_set(9, 0, b"")
+    s = cg.solve(b, x, maxit=0, stream=Stream(), raise_on_failure=False)
+    out.append(counts()[:2])
+""")
+    assert out == [[0, 0]] * 5
