@@ -386,10 +386,11 @@ int32_t tp_plan_group_kernel(const tp_plan* plan, int32_t group, int32_t call, t
  * the recursively updated residual r, or after maxit iterations
  * (TP_ERR_NOT_CONVERGED), or on a breakdown / non-finite value
  * (TP_ERR_NONFINITE).  Every iteration runs on the device without host
- * synchronisation; the host reads the solver state at least once per
- * check_every iterations (<= 0 selects 16), so up to check_every - 1
- * iterations' kernels run after convergence and return at once (with a V-cycle,
- * whose first graph is launched before the state is read, up to four).
+ * synchronisation; the host reads the solver state every check_every
+ * iterations (<= 0 selects 16), with a V-cycle every four when check_every is
+ * larger, so up to check_every - 1 iterations' kernels run after convergence
+ * and return at once (with a V-cycle, whose first graph is launched before the
+ * state is read, up to four).
  * Synchronises the stream before returning; summary (optional) receives the
  * iterations, whether it
  * converged and the final relative residual.  One solve at a time per

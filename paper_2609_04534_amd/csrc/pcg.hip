@@ -622,10 +622,11 @@ struct tp_pcg {
     int64_t nwg = 0;
     int64_t elems = 0;
     // captured iterations per preconditioner precision (F64, F32): exec_chunk
-    // of them in a graph, `launches` graphs to a chunk of check_every
-    hipGraphExec_t exec[2] = {nullptr, nullptr};
-    int exec_chunk[2] = {0, 0};
-    int launches = 1;
+    // of them in a graph; a chunk of the running solve is `launches` graphs and,
+    // when they do not make it up, one of its `rest` last iterations
+    hipGraphExec_t exec[2] = {nullptr, nullptr}, exec_rest[2] = {nullptr, nullptr};
+    int exec_chunk[2] = {0, 0}, rest_chunk[2] = {0, 0};
+    int launches = 1, rest = 0;
     // non-blocking solves (tp_pcg_begin / tp_pcg_poll)
     hipEvent_t ev = nullptr;    // recorded after each enqueued step
     hipStream_t stream = nullptr;
@@ -638,10 +639,15 @@ struct tp_pcg {
 
 namespace {
 
+void free_graphs(tp_pcg* s) {
+    for (auto* set : {&s->exec, &s->exec_rest})
+        for (hipGraphExec_t& ex : *set)
+            if (ex) (void)hipGraphExecDestroy(ex), ex = nullptr;
+}
+
 void free_pcg(tp_pcg* s) {
     if (s->ev) (void)hipEventDestroy(s->ev), s->ev = nullptr;
-    for (hipGraphExec_t& ex : s->exec)
-        if (ex) (void)hipGraphExecDestroy(ex), ex = nullptr;
+    free_graphs(s);
     for (void* ptr : {static_cast<void*>(s->r), static_cast<void*>(s->z), static_cast<void*>(s->p),
                       static_cast<void*>(s->q), static_cast<void*>(s->xw), static_cast<void*>(s->part),
                       static_cast<void*>(s->st)})
@@ -649,18 +655,13 @@ void free_pcg(tp_pcg* s) {
     if (s->host) (void)hipHostFree(s->host);
 }
 
-// Iterations per captured graph for a chunk of check_every: all of them with
+// Iterations of a captured graph for a chunk of them: the whole chunk with
 // block-Jacobi (its iterations take tens of microseconds and solves hundreds of
-// them), and the largest divisor up to 4 with a V-cycle, whose solves take
-// about ten iterations of many launches each: graphs of 16 spent 0.4 of 1.65
-// ms (p = 2, 16^3 cells, 7 iterations) in launches after convergence, and their
-// instantiation costs a new solver more than a millisecond.
-int graph_iterations(int chunk, bool multigrid) {
-    if (!multigrid) return chunk;
-    for (int k = 4; k > 1; --k)
-        if (chunk % k == 0) return k;
-    return 1;
-}
+// them), at most four with a V-cycle, whose solves take about ten iterations of
+// many launches each: graphs of 16 spent 0.4 of 1.65 ms (p = 2, 16^3 cells, 7
+// iterations) in launches after convergence, and their instantiation costs a new
+// solver more than a millisecond.
+int graph_iterations(const tp_pcg* s, int chunk) { return s->mg ? std::min(chunk, 4) : chunk; }
 
 // Enqueues the start of a solve on stream (x = x0 or 0, r, z, p and the
 // first reduction) and makes sure the iteration graph of this precision exists.
@@ -743,17 +744,16 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
     // the iterations, captured once per solver and precision: every argument is
     // solver-owned, so the graph replays for any b, x
     const int ti = sizeof(TI) == 8 ? 0 : 1;
-    const int sub = graph_iterations(chunk, s->mg != nullptr);
-    s->launches = chunk / sub;
-    if (!s->exec[ti] || s->exec_chunk[ti] != sub) {
-        if (s->exec[ti]) (void)hipGraphExecDestroy(s->exec[ti]), s->exec[ti] = nullptr;
+    auto capture = [&](hipGraphExec_t& exec, int& held, int iterations) -> tp_status {
+        if (exec && held == iterations) return TP_OK;
+        if (exec) (void)hipGraphExecDestroy(exec), exec = nullptr;
         hipStream_t cs = nullptr;
         hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
         if (e != hipSuccess) return hip_error(e, "PCG capture stream");
         hipGraph_t gr = nullptr;
         e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            for (int i = 0; i < sub; ++i) {
+            for (int i = 0; i < iterations; ++i) {
                 if constexpr (kLane) {
                     const dim3 wg(64, N), gr1(tile_grid(G, 1)), gr2(tile_grid(G, 2));
                     auto aq = [&](auto Hc) {
@@ -834,17 +834,23 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
             const hipError_t e2 = hipStreamEndCapture(cs, &gr);
             if (e2 != hipSuccess) e = e2;
         }
-        if (e == hipSuccess) e = hipGraphInstantiate(&s->exec[ti], gr, nullptr, nullptr, 0);
+        if (e == hipSuccess) e = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
         if (gr) (void)hipGraphDestroy(gr);
         (void)hipStreamDestroy(cs);
         if (e != hipSuccess) {
-            s->exec[ti] = nullptr;
+            exec = nullptr;
             return hip_error(e, "PCG iteration graph");
         }
-        s->exec_chunk[ti] = sub;
-    }
+        held = iterations;
+        return TP_OK;
+    };
+    const int sub = graph_iterations(s, chunk);
+    s->launches = chunk / sub;
+    s->rest = chunk % sub;
+    st = capture(s->exec[ti], s->exec_chunk[ti], sub);
+    if (st == TP_OK && s->rest > 0) st = capture(s->exec_rest[ti], s->rest_chunk[ti], s->rest);
     s->ti = ti;
-    return TP_OK;
+    return st;
 }
 
 template <typename TI>
@@ -973,7 +979,8 @@ tp_status tp_pcg_solve(tp_pcg* s, const double* b, double* x, int32_t x_is_zero,
         if (summary) *summary = tp_pcg_summary{0, 1, 0.0};
         return TP_OK;
     }
-    const int chunk = check_every > 0 ? check_every : 16;
+    // the state is read after every graph
+    const int chunk = graph_iterations(s, check_every > 0 ? check_every : 16);
     st = pcg_start(s, b, x, x_is_zero != 0, inner, rtol, maxit, chunk, stream);
     if (st != TP_OK) return st;
     // With a V-cycle a graph is short and the first is launched without reading
@@ -1048,6 +1055,7 @@ tp_status tp_pcg_poll(tp_pcg* s, tp_pcg_summary* summary) {
     } else {
         hipError_t e = hipSuccess;
         for (int i = 0; i < s->launches && e == hipSuccess; ++i) e = hipGraphLaunch(s->exec[s->ti], s->stream);
+        if (e == hipSuccess && s->rest > 0) e = hipGraphLaunch(s->exec_rest[s->ti], s->stream);
         st = e == hipSuccess ? enqueue_state_copy(s, s->stream) : hip_error(e, "PCG iteration graph launch");
     }
     if (st == TP_OK) {
@@ -1071,8 +1079,7 @@ tp_status tp_pcg_set_multigrid(tp_pcg* s, tp_mg* mg) {
     if (s->phase != 0) return set_error(TP_ERR_STATE, "a non-blocking solve is still running on this solver");
     if (mg && mg_plan(mg) != s->plan) return set_error(TP_ERR_ARG, "the multigrid belongs to another plan");
     s->mg = mg;
-    for (hipGraphExec_t& ex : s->exec)   // the captured iterations depend on the preconditioner
-        if (ex) (void)hipGraphExecDestroy(ex), ex = nullptr;
+    free_graphs(s);   // the captured iterations depend on the preconditioner
     return TP_OK;
 }
 

@@ -63,3 +63,33 @@ for m in (None, mg):
     out.append(counts()[:2])
 """)
     assert out == [[0, 0]] * 5
+
+
+def test_vcycle_solve_reads_the_state_every_four_iterations(stub):
+    """With a V-cycle the state is read after min(check_every, 4) iterations, for
+    every check_every (9 iterations to convergence; one synchronisation per
+    graph and one for the result), and a non-blocking solve enqueues exactly
+    check_every iterations a step."""
+    out = stub("""
+plan, b, x, cg = mesh(3, 4)
+mg = tpfdm.MG(plan)
+cg.set_multigrid(mg)
+for k in (1, 2, 3, 4, 5, 7, 13, 16, 17, 64):
+    stub.stub_set(9, 0, b"")
+    s = cg.solve(b, x, check_every=k, stream=Stream())
+    blocking = counts() + [s["iterations"]]
+    stub.stub_set(100, 0, b"")
+    cg.begin(b, x, check_every=k, stream=Stream())
+    steps = []
+    while cg.poll() is None:
+        steps.append(stub.stub_iterations())
+    out.append([k, blocking, steps])
+cg.destroy()
+out.append(stub.stub_live_graphs())
+""")
+    assert out.pop() == 0
+    for k, blocking, steps in out:
+        g = min(k, 4)
+        graphs = -(-9 // g)
+        assert blocking == [graphs, graphs * g, graphs + 1, 9], k
+        assert steps == [k * (i + 1) for i in range(-(-100 // k))] + [-(-100 // k) * k], k
