@@ -751,9 +751,10 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
         hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
         if (e != hipSuccess) return hip_error(e, "PCG capture stream");
         hipGraph_t gr = nullptr;
+        tp_status enqueued = TP_OK;
         e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            for (int i = 0; i < iterations; ++i) {
+            for (int i = 0; i < iterations && enqueued == TP_OK; ++i) {
                 if constexpr (kLane) {
                     const dim3 wg(64, N), gr1(tile_grid(G, 1)), gr2(tile_grid(G, 2));
                     auto aq = [&](auto Hc) {
@@ -807,7 +808,8 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                     };
                     if (r32) axpy(std::true_type{});
                     else axpy(std::false_type{});
-                    (void)mg_enqueue_iteration(s->mg, s->r, s->z, s->part, &rzcnt, s->st, f32, cs);
+                    enqueued = mg_enqueue_iteration(s->mg, s->r, s->z, s->part, &rzcnt, s->st, f32, cs);
+                    if (enqueued != TP_OK) break;
                 } else if constexpr (kLane)
                     hipLaunchKernelGGL((k_pcg_update<N, TI, LB>), dim3(nwg), dim3(64), 0, cs, s->xw, s->r, s->z,
                                        s->p, s->q, G, E, s->st, s->part, cnt);
@@ -830,13 +832,18 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                                        s->elems, s->st);
                 else
                     hipLaunchKernelGGL(k_pcg_dir<double>, dim3(dgrid), dim3(256), 0, cs, s->z, s->p, s->elems, s->st);
+                enqueued = check_launch("PCG iteration");
             }
             const hipError_t e2 = hipStreamEndCapture(cs, &gr);
             if (e2 != hipSuccess) e = e2;
         }
-        if (e == hipSuccess) e = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
+        if (e == hipSuccess && enqueued == TP_OK) e = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
         if (gr) (void)hipGraphDestroy(gr);
         (void)hipStreamDestroy(cs);
+        if (enqueued != TP_OK) {   // (no graph without one of its launches; the error is the launch's)
+            (void)hipGetLastError();
+            return enqueued;
+        }
         if (e != hipSuccess) {
             exec = nullptr;
             return hip_error(e, "PCG iteration graph");

@@ -93,3 +93,27 @@ out.append(stub.stub_live_graphs())
         graphs = -(-9 // g)
         assert blocking == [graphs, graphs * g, graphs + 1, 9], k
         assert steps == [k * (i + 1) for i in range(-(-100 // k))] + [-(-100 // k) * k], k
+
+
+@pytest.mark.parametrize("kernel", ["k_mg_restrict", "k_mg_smooth", "k_mg_tail", "k_pcg_aq", "k_pcg_axpy",
+                                    "k_pcg_reduce_alpha", "k_pcg_dir"])
+def test_failed_launch_in_an_iteration(stub, kernel):
+    """A launch that fails while the iterations are captured fails the solve
+    with that launch's error, leaves no graph without it, and the next solve
+    captures anew."""
+    out = stub("""
+plan, b, x, cg = mesh(3, 8)
+mg = tpfdm.MG(plan)
+cg.set_multigrid(mg)
+KERNEL = b"%s"
+for begin in (False, True):
+    stub.stub_set(9, 0, KERNEL)
+    try:
+        (cg.begin if begin else cg.solve)(b, x, stream=Stream())
+        out.append("no error")
+    except tpfdm.TpfdmError as e:
+        out.append([e.status, stub.stub_graph_launches(), stub.stub_live_graphs()])
+stub.stub_set(9, 0, b"")
+out.append([cg.solve(b, x, stream=Stream())["iterations"], stub.stub_live_graphs()])
+""" % kernel)
+    assert out == [[-7, 0, 0], [-7, 0, 0], [9, 1]]
