@@ -126,18 +126,17 @@ __device__ __forceinline__ void block_scales(const double* h, int64_t g, TC& sx,
 // as one, lane d dividing for direction d.  (Every lane dividing three times
 // took a fifth of the VALU instructions of a tile at n = 8.)  Bit for bit
 // block_scales.  Every lane of the wave must call it.
-__device__ __forceinline__ double wave_lengths(const double* h, int64_t g) {
-    return h[3 * g + (threadIdx.x < 3 ? threadIdx.x : 0)];
+__device__ __forceinline__ double wave_lengths(const double* h, int64_t g, int lane = threadIdx.x) {
+    return h[3 * g + (lane < 3 ? lane : 0)];
 }
 __device__ __forceinline__ double read_lane(double v, int lane) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                             __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 template <typename TC>
-__device__ __forceinline__ void wave_scales(double len, TC& sx, TC& sy, TC& sz) {
+__device__ __forceinline__ void wave_scales(double len, TC& sx, TC& sy, TC& sz, int lane = threadIdx.x) {
     const double hx = read_lane(len, 0), hy = read_lane(len, 1), hz = read_lane(len, 2);
-    const int d = threadIdx.x;
-    const double q = (d == 0 ? hy * hz : d == 1 ? hx * hz : hx * hy) / len;
+    const double q = (lane == 0 ? hy * hz : lane == 1 ? hx * hz : hx * hy) / len;
     sx = static_cast<TC>(read_lane(q, 0));
     sy = static_cast<TC>(read_lane(q, 1));
     sz = static_cast<TC>(read_lane(q, 2));
@@ -240,8 +239,7 @@ struct Pencil {
     bool act;    // lane owns a pencil of an existing block
     // n = 8: a tile is one block (there is always one) and every lane has a pencil
     static constexpr bool kFull = Slab<N>::N2 == 64;
-    __device__ __forceinline__ Pencil(int nvalid) {
-        const int lane = threadIdx.x;
+    __device__ __forceinline__ explicit Pencil(int nvalid, int lane = threadIdx.x) {
         w = lane / Slab<N>::N2;
         const int p = lane - w * Slab<N>::N2;
         pa = p / N;

@@ -226,8 +226,8 @@ __device__ __forceinline__ void load_table(TC (&dst)[COUNT], const TC* __restric
 
 // Stages COUNT table entries in LDS (stab) for reads from there.
 template <typename TC, int COUNT>
-__device__ __forceinline__ void stage_table(const TC* __restrict__ tab, TC* stab) {
-    for (int e = threadIdx.x; e < COUNT; e += 64) stab[e] = tab[e];
+__device__ __forceinline__ void stage_table(const TC* __restrict__ tab, TC* stab, int lane = threadIdx.x) {
+    for (int e = lane; e < COUNT; e += 64) stab[e] = tab[e];
     wave_sync();
 }
 
@@ -691,10 +691,9 @@ __device__ __forceinline__ void solve_tile_reg(const double* __restrict__ b, dou
                                                const GArgs& G, int64_t g0, int nvalid, SolveLdsR<N>& S,
                                                ApplyF apply_regs, InvF inverse_regs, double rtol, int maxit,
                                                int32_t* __restrict__ iters, double* __restrict__ relres,
-                                               int64_t block0, SolveAcc& acc) {
+                                               int64_t block0, SolveAcc& acc, int lane) {
     using L = Slab<N>;
-    const Pencil<N> pc(nvalid);
-    const int lane = threadIdx.x;
+    const Pencil<N> pc(nvalid, lane);
     const int so = (pc.w < L::BPW ? pc.w : 0) * L::size;
     double xr[N], br[N];
     bool nz = false;
@@ -839,13 +838,13 @@ __device__ __forceinline__ void eo_solve_tile(const double* __restrict__ b, doub
                                               int64_t g0, int nvalid, SolveLdsR<N>& S, const double* tA,
                                               const TI* tS, const TI* lam, double rtol, int maxit,
                                               int32_t* __restrict__ iters, double* __restrict__ relres,
-                                              int64_t block0, SolveAcc& acc) {
+                                              int64_t block0, SolveAcc& acc, int lane = threadIdx.x) {
     using E = EOShape<N>;
-    const Pencil<N> pc(nvalid);
+    const Pencil<N> pc(nvalid, lane);
     const UniTab<double> A{tA};
     const UniTab<TI> I{tS};
     double sx = 1.0, sy = 1.0, sz = 1.0;
-    if constexpr (Slab<N>::BPW == 1) wave_scales(wave_lengths(G.h, g0), sx, sy, sz);
+    if constexpr (Slab<N>::BPW == 1) wave_scales(wave_lengths(G.h, g0, lane), sx, sy, sz, lane);
     else if (pc.act) block_scales(G.h, g0 + pc.w, sx, sy, sz);
     const TI sxi = static_cast<TI>(sx), syi = static_cast<TI>(sy), szi = static_cast<TI>(sz);
     solve_tile_reg<N, TI, RND, VP>(
@@ -857,7 +856,7 @@ __device__ __forceinline__ void eo_solve_tile(const double* __restrict__ b, doub
         [&](const Pencil<N>& p, TI (&d)[N], TI* slab) {
             eo_inverse_regs<N, TI>(p, d, slab, I, I + E::SE, lam, sxi, syi, szi);
         },
-        rtol, maxit, iters, relres, block0, acc);
+        rtol, maxit, iters, relres, block0, acc, lane);
 }
 
 // Copies `count` table entries to LDS (always: the eigenvalues are indexed

@@ -225,19 +225,25 @@ __device__ __forceinline__ void seg_solve(const double* b, double* x, const PSeg
     SolveLdsR<N>& L = *reinterpret_cast<SolveLdsR<N>*>(lds);
     TI* stabS = reinterpret_cast<TI*>(lds + sizeof(SolveLdsR<N>));
     // 1D tables read at wave-uniform addresses (scalar loads), the
-    // eigenvalues through LDS (as in the per-group solve kernel)
-    const double* tA = reinterpret_cast<const double*>(dev_table(tabs, N, EO_APPLY_A, 0));
-    const TI* tS = reinterpret_cast<const TI*>(dev_table(tabs, N, EO_INV, sizeof(TI) == 8 ? 0 : 1));
-    stage_table<TI, S::SE + S::SO + N>(tS, stabS);
+    // eigenvalues through LDS (as in the per-group solve kernel).  Lane and
+    // tables are opaque to the compiler per item: it would otherwise compute
+    // every degree's lane offsets and load every degree's tables before the loop
+    // over the items and keep them all (253 to 256 VGPRs with spills and two
+    // waves per SIMD; 155 to 167 and three so).  60000 blocks of p = 2, 3 and 7,
+    // FP64 / FP32 inner: 161 / 212 us with that, 132 / 155 us; 60000 of p = 5, 6
+    // and 7: 320 / 458 and 242 / 301 us.
+    auto ct = (const char __attribute__((address_space(4)))*)tabs;   // (constant: scalar loads)
+    int lane = threadIdx.x;
+    asm volatile("" : "+s"(ct), "+v"(lane));
+    const double* tA = reinterpret_cast<const double*>(dev_table((const char*)ct, N, EO_APPLY_A, 0));
+    const TI* tS = reinterpret_cast<const TI*>(dev_table((const char*)ct, N, EO_INV, sizeof(TI) == 8 ? 0 : 1));
+    stage_table<TI, S::SE + S::SO + N>(tS, stabS, lane);
     const TI* lam = stabS + S::SE + S::SO;
     const GArgs G = seg_args(sg);
     for (int64_t t = t0; t < t1; ++t)
         eo_solve_tile<N, TI, RND, false>(b, x, G, t * Slab<N>::BPW, nvalid_of<N>(G, t), L, tA, tS, lam, rtol,
-                                         maxit, iters, relres, sg.block0, acc);
+                                         maxit, iters, relres, sg.block0, acc, lane);
 }
-
-
-
 
 // Segment of work item w: segments in launch order, each covering the items
 // [first_item, first_item + ceil(tiles / tpw)) of the launch.
@@ -303,7 +309,7 @@ __global__ __launch_bounds__(64, 2) void k_persist_inverse(const TS* __restrict_
 // The solve over all groups: workgroups walk the item list with the grid
 // stride, the group's body inlined per degree.
 template <typename TI, int RND>
-__global__ __launch_bounds__(64, 2) void k_persist_solve(const double* __restrict__ b, double* __restrict__ x,
+__global__ __launch_bounds__(64, 3) void k_persist_solve(const double* __restrict__ b, double* __restrict__ x,
                                                          const PSeg* __restrict__ segs, int nseg,
                                                          const char* __restrict__ tabs, double rtol, int maxit,
                                                          int32_t* __restrict__ iters, double* __restrict__ relres,
