@@ -61,8 +61,10 @@ __device__ __forceinline__ unsigned lane_tile(unsigned b, unsigned nwg, unsigned
 // The one-cell-per-wave kernels (n >= 5) sweep groups of 192 cells (n = 8 in
 // FP64 on 48^3 cells: 397 us in plain order, 374, 367, 368 and 373 us with 48,
 // 192, 384 and 768; FP32 and smaller n within 2%).
+// WV > 1 (workgroups of WV waves, one cell each): groups of as many cells.
+template <int WV = 1>
 __device__ __forceinline__ unsigned wave_tile(unsigned b, unsigned nwg, const MeshArgs& G) {
-    return sweep_tile(b, nwg, static_cast<unsigned>(G.my) * static_cast<unsigned>(G.mz), 192);
+    return sweep_tile(b, nwg, static_cast<unsigned>(G.my) * static_cast<unsigned>(G.mz) / WV, 192 / WV);
 }
 
 // Row length S for lane_tile: the whole tiles of 64 W cells in an x-plane of

@@ -164,12 +164,13 @@ __device__ __forceinline__ void wave_sipg_cell(const T* __restrict__ u, const Me
         for (int t = 1; t < LV; ++t) al = fma(cf[t], v[t], al);
         be = rev ? -v[0] : v[0];
     };
-    // x and y faces: lane (a, b) reads its pencil along the normal (stride ST)
+    // lane (a, b) reads its pencil along the normal (stride ST)
     auto face = [&](auto STc, auto UPc, bool interior, int64_t d, T& al, T& be) {
         constexpr int ST = decltype(STc)::value;
         constexpr bool UP = decltype(UPc)::value;
         const bool rev = UP != interior;
-        const int q0 = (ST == N * N ? pa * N + pb : pa * N * N + pb) + (rev ? (N - 1) * ST : 0);
+        const int q0 = (ST == N * N ? pa * N + pb : ST == N ? pa * N * N + pb : (pa * N + pb) * N) +
+                       (rev ? (N - 1) * ST : 0);
         const int step = rev ? -ST : ST;
         const T* p = ub + block_base(interior ? c + d : c, lb, N3) + (static_cast<int64_t>(q0) << lb);
         T v[N];
@@ -229,6 +230,11 @@ __device__ __forceinline__ void wave_sipg_cell(const T* __restrict__ u, const Me
         o += ra * FR + rb;
         o[0] = f.ap, o[FS] = f.am, o[2 * FS] = f.bd, o[3 * FS] = f.bs;
     };
+    // The z neighbours' pencils come whole where 16-byte loads fetch them, and in
+    // the Lagrange basis, which weighs every layer.  Else two layers of each are
+    // enough: whole pencils took 2 n loads a lane more for nothing (28^3 cells at
+    // B = 64, FP64, n = 6: 80 us against 68).
+    constexpr bool kZLayers = HERM && !VP;
     const bool xl = cx > 0, xh = cx + 1 < static_cast<uint32_t>(G.mx);
     const bool yl = cy > 0, yh = cy + 1 < static_cast<uint32_t>(G.my);
     const bool zl = cz > 0, zh = cz + 1 < static_cast<uint32_t>(G.mz);
@@ -237,28 +243,37 @@ __device__ __forceinline__ void wave_sipg_cell(const T* __restrict__ u, const Me
         const int64_t zp = static_cast<int64_t>((pa * N + pb) * N) << lb;
         pencil_load<N, VP>(x, ub + block_base(c, lb, N3) + zp, lb);
         T wl[N], wh[N];
-        pencil_load<N, VP>(wl, ub + block_base(zl ? c - 1 : c, lb, N3) + zp, lb);
-        pencil_load<N, VP>(wh, ub + block_base(zh ? c + 1 : c, lb, N3) + zp, lb);
+        if constexpr (kZLayers) {
+            face(std::integral_constant<int, 1>{}, std::integral_constant<bool, false>{}, zl, -1, zal, zbl);
+            face(std::integral_constant<int, 1>{}, std::integral_constant<bool, true>{}, zh, 1, zah, zbh);
+        } else {
+            pencil_load<N, VP>(wl, ub + block_base(zl ? c - 1 : c, lb, N3) + zp, lb);
+            pencil_load<N, VP>(wh, ub + block_base(zh ? c + 1 : c, lb, N3) + zp, lb);
+        }
         axis(std::integral_constant<int, N>{}, fs, yl, yh, static_cast<int64_t>(G.mz));
         axis(std::integral_constant<int, N * N>{}, fs + 4 * FS, xl, xh, syz);
 #pragma unroll
-        for (int k = 0; k < N; ++k) {
-            if (HERM) x[k] *= sab * sg(k), wl[k] *= sab * sg(k), wh[k] *= sab * sg(k);
-        }
-        // z faces, layers counted from the face (lower: reversed when interior)
-        T rl[N], rh[N];
+        for (int k = 0; k < N; ++k)
+            if (HERM) x[k] *= sab * sg(k);
+        if constexpr (!kZLayers) {
+            // z faces, layers counted from the face (lower: reversed when interior)
 #pragma unroll
-        for (int t = 0; t < N; ++t) rl[t] = wl[N - 1 - t], rh[t] = wh[N - 1 - t];
-        if constexpr (N == 8) {   // uniform branches; n = 5 and 6 are 4% faster with selects
-            if (zl) reduce(rl, true, true, zal, zbl);
-            else reduce(wl, false, false, zal, zbl);
-            if (zh) reduce(wh, true, false, zah, zbh);
-            else reduce(rh, false, true, zah, zbh);
-        } else {
+            for (int k = 0; k < N; ++k)
+                if (HERM) wl[k] *= sab * sg(k), wh[k] *= sab * sg(k);
+            T rl[N], rh[N];
 #pragma unroll
-            for (int t = 0; t < N; ++t) rl[t] = zl ? rl[t] : wl[t], rh[t] = zh ? wh[t] : rh[t];
-            reduce(rl, zl, zl, zal, zbl);
-            reduce(rh, zh, !zh, zah, zbh);
+            for (int t = 0; t < N; ++t) rl[t] = wl[N - 1 - t], rh[t] = wh[N - 1 - t];
+            if constexpr (N == 8) {   // uniform branches; n = 5 and 6 are 4% faster with selects
+                if (zl) reduce(rl, true, true, zal, zbl);
+                else reduce(wl, false, false, zal, zbl);
+                if (zh) reduce(wh, true, false, zah, zbh);
+                else reduce(rh, false, true, zah, zbh);
+            } else {
+#pragma unroll
+                for (int t = 0; t < N; ++t) rl[t] = zl ? rl[t] : wl[t], rh[t] = zh ? wh[t] : rh[t];
+                reduce(rl, zl, zl, zal, zbl);
+                reduce(rh, zh, !zh, zah, zbh);
+            }
         }
     }
     wave_sync();

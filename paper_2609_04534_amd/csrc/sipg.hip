@@ -23,12 +23,23 @@ __global__ __launch_bounds__(64 * N, (tile_waves<N, TC, W>())) void k_sipg_tile(
     for (int q = 0; q < N2; ++q) st_cells<NT>(vb + (static_cast<int64_t>(q) << lb), out[q]);
 }
 
+// Waves per workgroup of the one-cell-per-wave kernel.  From B = 8 on the cells
+// of a layout tile share every cache line of their blocks, so eight neighbours
+// run on one CU and its vector cache serves a line to all of them; one to a
+// workgroup, each CU fetched the line for one cell.  28^3 cells, FP64, one wave
+// against eight: B = 8 n = 6 86 / 70 us, n = 8 302 / 170 us; B = 64 n = 6 134 /
+// 92 us, n = 8 480 / 303 us.  Below kTileCells cells too few CUs get any (B = 8,
+// FP64, n = 8: 512 cells 11 / 16 us, 1452 cells 24 / 18 us).
+constexpr int kTileWaves = 8;
+constexpr int64_t kTileCells = 1024;
+
 // One cell per wave (n >= 5); HERM: the Hermite-type basis.
-template <int N, typename T, bool VP, bool HERM>
-__global__ __launch_bounds__(64, 2) void k_sipg_wave(const T* __restrict__ u, T* __restrict__ v, MeshArgs G,
+template <int N, typename T, bool VP, bool HERM, int WV = 1>
+__global__ __launch_bounds__(64 * WV, 2) void k_sipg_wave(const T* __restrict__ u, T* __restrict__ v, MeshArgs G,
                                                   const T* __restrict__ tab, WaveFace<N, T> F) {
     constexpr int TAB = 2 * (EOShape<N>::SE + EOShape<N>::SO);
-    __shared__ WaveLds<N, T> L;
+    __shared__ WaveLds<N, T> L[WV];
+    const int wave = WV == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.y);
     // FP64: the tables are read at wave-uniform global addresses (scalar
     // loads; in VGPRs they would take half the register file, from LDS they
     // would compete with the slab traffic); FP32: from registers
@@ -39,13 +50,15 @@ __global__ __launch_bounds__(64, 2) void k_sipg_wave(const T* __restrict__ u, T*
     } else {
         load_table<T, TAB>(TB, tab, nullptr);   // FP32: straight from the global table
     }
-    const int64_t c = wave_tile(blockIdx.x, gridDim.x, G);
+    const int64_t c = static_cast<int64_t>(wave_tile<WV>(blockIdx.x, gridDim.x, G)) * WV + wave;
+    if (WV > 1 && c >= G.ncells) return;   // (waves of a workgroup share nothing)
     T y[N];
-    wave_sipg_cell<N, T, VP, HERM>(u, G, tb, F, c, L, y);
+    wave_sipg_cell<N, T, VP, HERM>(u, G, tb, F, c, L[wave], y);
     const Pencil<N> pc(1);
     if (pc.act) {
         T* vb = v + G.offset + block_base(c, G.logB, N * N * N);
-        constexpr bool kWholeLines = (N * N * sizeof(T)) % 128 == 0;
+        // streamed where a plane is whole lines of this cell alone
+        constexpr bool kWholeLines = WV == 1 && (N * N * sizeof(T)) % 128 == 0;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             T* o = vb + (static_cast<int64_t>((i * N + pc.pa) * N + pc.pb) << G.logB);
@@ -93,16 +106,18 @@ tp_status sipg_wave_n(const Plan& plan, const MeshArgs& G, bool face_only, const
     // 16-byte pencils: block-contiguous layout and an aligned vector
     const bool vp = G.logB == 0 && (reinterpret_cast<uintptr_t>(ui + G.offset) % 16 == 0) &&
                     (N * sizeof(T)) % 16 == 0;
-    if (plan.basis == TP_BASIS_HERMITE) {
+    auto launch = [&](auto Hc) {
+        constexpr bool HERM = decltype(Hc)::value;
         if (vp)
-            hipLaunchKernelGGL((k_sipg_wave<N, T, true, true>), dim3(grid), dim3(64), 0, s, ui, vo, G, tab, F);
+            hipLaunchKernelGGL((k_sipg_wave<N, T, true, HERM>), dim3(grid), dim3(64), 0, s, ui, vo, G, tab, F);
+        else if (G.logB < 3 || G.ncells < kTileCells)
+            hipLaunchKernelGGL((k_sipg_wave<N, T, false, HERM>), dim3(grid), dim3(64), 0, s, ui, vo, G, tab, F);
         else
-            hipLaunchKernelGGL((k_sipg_wave<N, T, false, true>), dim3(grid), dim3(64), 0, s, ui, vo, G, tab, F);
-    } else if (vp) {
-        hipLaunchKernelGGL((k_sipg_wave<N, T, true, false>), dim3(grid), dim3(64), 0, s, ui, vo, G, tab, F);
-    } else {
-        hipLaunchKernelGGL((k_sipg_wave<N, T, false, false>), dim3(grid), dim3(64), 0, s, ui, vo, G, tab, F);
-    }
+            hipLaunchKernelGGL((k_sipg_wave<N, T, false, HERM, kTileWaves>), dim3((grid + kTileWaves - 1) / kTileWaves),
+                               dim3(64, kTileWaves), 0, s, ui, vo, G, tab, F);
+    };
+    if (plan.basis == TP_BASIS_HERMITE) launch(std::true_type{});
+    else launch(std::false_type{});
     return check_launch("SIPG apply launch");
 }
 
