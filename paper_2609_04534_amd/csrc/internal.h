@@ -251,10 +251,8 @@ tp_status launch_inverse_persistent(const Plan& plan, const void* r, void* x, tp
 tp_status launch_solve_persistent(const Plan& plan, const double* b, double* x, tp_dtype inner, double rtol,
                                   int maxit, int32_t* iters, double* relres, const SolveWork& w, int64_t* nparts,
                                   hipStream_t s);
-// Multigrid V-cycle of a mesh plan (mg.hip): u = V(b) on the finest level,
-// every kernel skipped once the PCG state st (nullable) is done; the dot
-// kernel writes per-tile partials of (a, b).
-tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, const void* st, bool f32, hipStream_t s);
+// Multigrid V-cycle of a mesh plan (mg.hip): u = V(b) on the finest level.
+tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, bool f32, hipStream_t s);
 // With FP32 level storage the V-cycle's result stays on the device in the
 // hierarchy's finest FP32 vector (u may then be null): mg_result32 returns
 // it, mg_enqueue_widen copies it to an FP64 vector; null / TP_ERR_STATE for
@@ -262,13 +260,15 @@ tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, const vo
 int mg_storage(const tp_mg* m);
 const float* mg_result32(const tp_mg* m);
 // The V-cycle of a CG iteration, z = V(r), with *count partials of (r, z) in
-// part (at most one per 64 cells for n <= 4, one per cell above).  With FP32
-// level storage the caller has put r into mg_rhs32 and z stays in mg_result32.
+// part (at most one per 64 cells for n <= 4, one per cell above), every kernel
+// skipped once the PCG state st is done.  With FP32 level storage the caller has
+// put r into mg_rhs32 and z stays in mg_result32.
 float* mg_rhs32(const tp_mg* m);
 tp_status mg_enqueue_iteration(const tp_mg* m, const double* r, double* z, double* part, int64_t* count, const void* st,
                                bool f32, hipStream_t s);
 tp_status mg_enqueue_widen(const tp_mg* m, double* dst, hipStream_t s);
-// Partial (a, b) per 64-cell tile with b in FP64 or (b32) FP32.
+// Partials of (a, b), per 64-cell tile (n <= 4) or cell, with b in FP64 or (b32)
+// FP32; skipped once st (nullable) is done.
 tp_status mg_enqueue_dot(const tp_mg* m, const double* a, const void* b, bool b32, double* part, const void* st,
                          hipStream_t s);
 const tp_plan* mg_plan(const tp_mg* m);

@@ -919,9 +919,7 @@ DegTab<N> deg_table() {
 // hold cells: the caller's padding lanes are not written.
 template <typename TD, typename TSRC>
 __global__ __launch_bounds__(256) void k_mg_convert(const TSRC* __restrict__ src, TD* __restrict__ dst, int64_t n,
-                                                    int64_t full, int mask, int rest,
-                                                    const PcgState* __restrict__ st) {
-    if (done_flag(st)) return;
+                                                    int64_t full, int mask, int rest) {
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * 256)
         if (i < full || (static_cast<int>(i) & mask) < rest) dst[i] = static_cast<TD>(src[i]);
@@ -1360,7 +1358,7 @@ void launch_dot_wave(const MgLevel& L, const double* a, const void* b, bool b32,
                            L.G, part, ps);
 }
 
-tp_status convert_launch(const void* src, void* dst, bool to_f32, const tp_mg* m, const PcgState* st, hipStream_t s) {
+tp_status convert_launch(const void* src, void* dst, bool to_f32, const tp_mg* m, hipStream_t s) {
     const MgLevel& L = m->lv[0];
     const int64_t n = L.elems, n3 = int64_t(m->n) * m->n * m->n;
     const int64_t full = (L.G.ncells >> L.G.logB) * n3 << L.G.logB;
@@ -1368,10 +1366,10 @@ tp_status convert_launch(const void* src, void* dst, bool to_f32, const tp_mg* m
     const unsigned grid = static_cast<unsigned>(std::min<int64_t>((n + 255) / 256, 8192));
     if (to_f32)
         hipLaunchKernelGGL((k_mg_convert<float, double>), dim3(grid), dim3(256), 0, s, static_cast<const double*>(src),
-                           static_cast<float*>(dst), n, full, mask, rest, st);
+                           static_cast<float*>(dst), n, full, mask, rest);
     else
         hipLaunchKernelGGL((k_mg_convert<double, float>), dim3(grid), dim3(256), 0, s, static_cast<const float*>(src),
-                           static_cast<double*>(dst), n, full, mask, rest, st);
+                           static_cast<double*>(dst), n, full, mask, rest);
     return check_launch("multigrid conversion");
 }
 
@@ -1397,16 +1395,15 @@ tp_status vcycle_on_level(const tp_mg* m, const double* b, double* u, const PcgS
 }
 }  // namespace
 
-tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, const void* st, bool f32, hipStream_t s) {
-    const PcgState* ps = static_cast<const PcgState*>(st);
-    if (m->storage != TP_F32) return vcycle_on_level(m, b, u, ps, f32, s, nullptr);
+tp_status mg_enqueue_vcycle(const tp_mg* m, const double* b, double* u, bool f32, hipStream_t s) {
+    if (m->storage != TP_F32) return vcycle_on_level(m, b, u, nullptr, f32, s, nullptr);
     // b into the hierarchy's FP32 right-hand side, the cycle, and (when u is
     // given) the FP32 result back to FP64
     const MgLevel& L0 = m->lv[0];
-    tp_status r = convert_launch(b, L0.b, true, m, ps, s);
-    if (r == TP_OK) r = vcycle_on_level(m, nullptr, nullptr, ps, f32, s, nullptr);
+    tp_status r = convert_launch(b, L0.b, true, m, s);
+    if (r == TP_OK) r = vcycle_on_level(m, nullptr, nullptr, nullptr, f32, s, nullptr);
     if (r != TP_OK || !u) return r;
-    return convert_launch(L0.u, u, false, m, ps, s);
+    return convert_launch(L0.u, u, false, m, s);
 }
 
 tp_status mg_enqueue_iteration(const tp_mg* m, const double* r, double* z, double* part, int64_t* count, const void* st,
@@ -1471,7 +1468,7 @@ tp_status mg_enqueue_dot(const tp_mg* m, const double* a, const void* b, bool b3
 
 tp_status mg_enqueue_widen(const tp_mg* m, double* dst, hipStream_t s) {
     if (m->storage != TP_F32) return set_error(TP_ERR_STATE, "the multigrid stores its levels in FP64");
-    return convert_launch(m->lv[0].u, dst, false, m, nullptr, s);
+    return convert_launch(m->lv[0].u, dst, false, m, s);
 }
 
 const tp_plan* mg_plan(const tp_mg* m) { return m->plan; }
@@ -1632,7 +1629,7 @@ tp_status tp_mg_vcycle(tp_mg* m, const double* b, double* x, hipStream_t stream)
     if (!m) return set_error(TP_ERR_ARG, "multigrid is null");
     if (!b || !x) return set_error(TP_ERR_ARG, "b and x must be non-null");
     if (static_cast<const void*>(b) == static_cast<const void*>(x)) return set_error(TP_ERR_ARG, "b and x must not alias");
-    return mg_enqueue_vcycle(m, b, x, nullptr, false, stream);
+    return mg_enqueue_vcycle(m, b, x, false, stream);
 }
 
 tp_status tp_mg_destroy(tp_mg* m) {

@@ -696,7 +696,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
             // with FP32 level storage z stays in the hierarchy's FP32 vector
             const bool z32 = mg_storage(s->mg) == TP_F32;
             const void* zp = z32 ? static_cast<const void*>(mg_result32(s->mg)) : static_cast<const void*>(s->z);
-            tp_status st = mg_enqueue_vcycle(s->mg, s->r, z32 ? nullptr : s->z, nullptr, f32, stream);
+            tp_status st = mg_enqueue_vcycle(s->mg, s->r, z32 ? nullptr : s->z, f32, stream);
             if (st == TP_OK) st = mg_enqueue_dot(s->mg, s->r, zp, z32, s->part, nullptr, stream);
             if (st != TP_OK) return st;
             if (z32) {
@@ -716,7 +716,7 @@ tp_status pcg_prepare(const Plan& plan, const GroupInfo& g, tp_pcg* s, const dou
                                    x_zero ? nullptr : s->q, x, s->xw, s->r, G, s->part, cnt);
             const bool z32 = mg_storage(s->mg) == TP_F32;
             const void* zp = z32 ? static_cast<const void*>(mg_result32(s->mg)) : static_cast<const void*>(s->z);
-            tp_status st = mg_enqueue_vcycle(s->mg, s->r, z32 ? nullptr : s->z, nullptr, f32, stream);
+            tp_status st = mg_enqueue_vcycle(s->mg, s->r, z32 ? nullptr : s->z, f32, stream);
             if (st == TP_OK) st = mg_enqueue_dot(s->mg, s->r, zp, z32, s->part, nullptr, stream);
             if (st != TP_OK) return st;
             if (z32) {
