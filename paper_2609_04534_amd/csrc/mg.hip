@@ -80,10 +80,11 @@ __global__ __launch_bounds__(64 * N, (tile_waves<N, MgTC<TS>, W>())) void k_mg_a
 }
 
 // u = omega D^{-1} b: the first Chebyshev update from u = 0 (no operator
-// application), the block inverse (E holds omega) in precision TI.
+// application), the block inverse in precision TI, its weight in FP64.
 template <int N, typename TI, typename TS>
 __global__ __launch_bounds__(64 * N, 4) void k_mg_jacobi0(const TS* __restrict__ b, TS* __restrict__ u, MeshArgs G,
-                                                          TileInv<N, TI> E, const PcgState* __restrict__ st) {
+                                                          TileInv<N, TI> E, double omega,
+                                                          const PcgState* __restrict__ st) {
     if (done_flag(st)) return;
     constexpr int N2 = N * N, N3 = N * N * N;
     __shared__ Cells<TI, 1> A[N3][64];
@@ -95,13 +96,13 @@ __global__ __launch_bounds__(64 * N, 4) void k_mg_jacobi0(const TS* __restrict__
     tile_fdm<N, TI, 1>(E, T, A, v);
     if (!T.valid) return;
 #pragma unroll
-    for (int e = 0; e < N2; ++e) u[base + (e << 6)] = static_cast<TS>(v[e].v[0]);
+    for (int e = 0; e < N2; ++e) u[base + (e << 6)] = static_cast<TS>(omega * static_cast<double>(v[e].v[0]));
 }
 
 // One Chebyshev update in a single pass (the factorized form: no residual
 // vector is stored): u_out = u_in + omega D^{-1} (b - A u_in) for the
 // workgroup's cells, A u_in from the cells and their six neighbours, the block
-// inverse (E holds omega) in precision TI on the residual planes.  u_out must
+// inverse in precision TI on the residual planes, the update in FP64.  u_out must
 // not alias u_in (other workgroups still read u_in).
 // DOT: also a partial of (r, u_out) per workgroup, for CG: r is read once more
 // here (64^3 cells, n = 4, FP64: 116 -> 132 us), where a kernel of its own read
@@ -109,7 +110,8 @@ __global__ __launch_bounds__(64 * N, 4) void k_mg_jacobi0(const TS* __restrict__
 template <int N, typename TI, bool HERM, typename TS, int W = 1, bool DOT = false>
 __global__ __launch_bounds__(64 * N, (tile_waves<N, MgTC<TS>, W>())) void k_mg_smooth(
     const TS* __restrict__ b, const TS* __restrict__ uin, TS* __restrict__ uout, MeshArgs G, TileTab<N, MgTC<TS>, HERM> R,
-    TileInv<N, TI> E, const PcgState* __restrict__ st, const double* __restrict__ r, double* __restrict__ part) {
+    TileInv<N, TI> E, double omega, const PcgState* __restrict__ st, const double* __restrict__ r,
+    double* __restrict__ part) {
     using TC = MgTC<TS>;
     if (done_flag(st)) return;
     constexpr int N2 = N * N, N3 = N * N * N;
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(64 * N, (tile_waves<N, MgTC<TS>, W>())) void k_mg_s
         for (int e = 0; e < N2; ++e) {
             Cells<double, W> uv = ld_cells<double, W>(uin + base + (e << 6));
 #pragma unroll
-            for (int k = 0; k < W; ++k) uv.v[k] += static_cast<double>(v[e].v[k]);
+            for (int k = 0; k < W; ++k) uv.v[k] = ::fma(omega, static_cast<double>(v[e].v[k]), uv.v[k]);
             st_cells<false>(uout + base + (e << 6), uv);
             if constexpr (DOT) {
                 const Cells<double, W> rv = ld_cells<double, W>(r + base + (e << 6));
@@ -347,7 +349,7 @@ struct TailArgs {
     int n0;                           // unknowns of the coarsest level
     MeshArgs G[kTailLevels];
     TileTab<N, MgTC<TS>, HERM> R;
-    TileInv<N, TI> E[kTailLevels - 1];   // of D^{-1} (no weight)
+    TileInv<N, TI> E[kTailLevels - 1];
     ProlTab<N> P, PT;
     double omega[3];
     const double* inv;
@@ -1052,7 +1054,7 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
         M.R = R;
         for (int i = 0; i < M.levels; ++i) {
             M.G[i] = m->lv[l + i].G;
-            if (i + 1 < M.levels) M.E[i] = tile_inv<N, TI>(plan.ref[N], M.G[i], 1.0);
+            if (i + 1 < M.levels) M.E[i] = tile_inv<N, TI>(plan.ref[N], M.G[i]);
         }
         prolongation_tables<N>(plan, M.P, M.PT);
         for (int j = 0; j < 3; ++j) M.omega[j] = m->omega[j];
@@ -1060,8 +1062,7 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
         hipLaunchKernelGGL((k_mg_tail<N, TI, HERM, TS>), dim3(1), dim3(64, N), 0, s, b, u, M, st);
         return check_launch("coarse levels");
     }
-    TileInv<N, TI> E[3];
-    for (int j = 0; j < 3; ++j) E[j] = tile_inv<N, TI>(plan.ref[N], L.G, m->omega[j]);
+    const TileInv<N, TI> E = tile_inv<N, TI>(plan.ref[N], L.G);
     ProlTab<N> P, PT;
     prolongation_tables<N>(plan, P, PT);
     const bool pairs = tile_pairs(L.G, sizeof(TS), reinterpret_cast<uintptr_t>(b) % 16 == 0 &&
@@ -1072,12 +1073,12 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
         if constexpr (sizeof(TS) == 8) {
             if (pairs) {
                 hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS, 2>), dim3(tile_grid(L.G, 2)), dim3(64, N), 0, s, b,
-                                   from, to, L.G, R, E[j], st, nullptr, nullptr);
+                                   from, to, L.G, R, E, m->omega[j], st, nullptr, nullptr);
                 return;
             }
         }
-        hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS>), dim3(grid), dim3(64, N), 0, s, b, from, to, L.G, R, E[j],
-                           st, nullptr, nullptr);
+        hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS>), dim3(grid), dim3(64, N), 0, s, b, from, to, L.G, R, E,
+                           m->omega[j], st, nullptr, nullptr);
     };
     // the last update, with the partials of (r, u) when they are asked for
     auto last_step = [&](const TS* from, TS* to, int j) {
@@ -1086,15 +1087,16 @@ tp_status vcycle_level(const tp_mg* m, size_t l, const TS* b, TS* u, const PcgSt
             if (pairs) {
                 rz->count = tile_grid(L.G, 2);
                 hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS, 2, true>), dim3(tile_grid(L.G, 2)), dim3(64, N), 0, s,
-                                   b, from, to, L.G, R, E[j], st, rz->r, rz->part);
+                                   b, from, to, L.G, R, E, m->omega[j], st, rz->r, rz->part);
                 return;
             }
         }
         rz->count = grid;
         hipLaunchKernelGGL((k_mg_smooth<N, TI, HERM, TS, 1, true>), dim3(grid), dim3(64, N), 0, s, b, from, to, L.G, R,
-                           E[j], st, rz->r, rz->part);
+                           E, m->omega[j], st, rz->r, rz->part);
     };
-    hipLaunchKernelGGL((k_mg_jacobi0<N, TI, TS>), dim3(grid), dim3(64, N), 0, s, b, u, L.G, E[0], st);
+    hipLaunchKernelGGL((k_mg_jacobi0<N, TI, TS>), dim3(grid), dim3(64, N), 0, s, b, u, L.G, E,
+                       m->omega[0], st);
     step(u, Lt, 1);
     step(Lt, u, 2);
     const MgLevel& C = m->lv[l + 1];

@@ -477,7 +477,7 @@ struct TileInv {
     TI d[N * N * N];
 };
 
-// v <- D^{-1} v (times E's omega) for the lane's cells, v the plane i = w in
+// v <- D^{-1} v for the lane's cells, v the plane i = w in
 // and out (fast diagonalization: S^T along z and y in the plane, along x
 // through LDS, the scaling, and back).  A: N^3 x 64 W values of TI, whose
 // plane i = w the wave owns on entry (and again on return).
@@ -562,17 +562,17 @@ inline bool tile_pairs(const MeshArgs& G, size_t elem, bool aligned) {
 // Workgroups of a tile kernel over a mesh's cells.
 inline unsigned tile_grid(const MeshArgs& G, int W) { return static_cast<unsigned>((G.ncells + 64 * W - 1) / (64 * W)); }
 
-// Tables of omega D^{-1} on a mesh level with the scalings of G, formed in
+// Tables of D^{-1} on a mesh level with the scalings of G, formed in
 // FP64 and rounded once.
 template <int N, typename TI>
-TileInv<N, TI> tile_inv(const RefData& ref, const MeshArgs& G, double omega) {
+TileInv<N, TI> tile_inv(const RefData& ref, const MeshArgs& G) {
     TileInv<N, TI> E;
     for (int e = 0; e < N * N; ++e) E.s[e] = static_cast<TI>(ref.S[e]);
     for (int i = 0; i < N; ++i)
         for (int j = 0; j < N; ++j)
             for (int k = 0; k < N; ++k)
                 E.d[(i * N + j) * N + k] =
-                    static_cast<TI>(omega / (ref.lam[i] * G.sx + ref.lam[j] * G.sy + ref.lam[k] * G.sz));
+                    static_cast<TI>(1.0 / (ref.lam[i] * G.sx + ref.lam[j] * G.sy + ref.lam[k] * G.sz));
     return E;
 }
 

@@ -32,6 +32,9 @@ Graph* capture = nullptr;
 hipError_t last = hipSuccess;
 std::string fail;
 int converge_at = 1 << 30, start_done = 0;
+std::string watch;
+int watch_arg = 0;
+std::vector<char> watched;
 int graph_launches = 0, iterations = 0, syncs = 0, live_execs = 0;
 
 State* run(const Step& s) {
@@ -56,6 +59,12 @@ void stub_set(int converge, int done_at_start, const char* fail_in_capture) {
     fail = fail_in_capture;
     graph_launches = iterations = syncs = 0;
 }
+void stub_watch(const char* kernel, int arg, int bytes) {   // keep an argument of the last launch of a kernel
+    watch = kernel;
+    watch_arg = arg;
+    watched.assign(static_cast<size_t>(bytes), 0);
+}
+void stub_watched(void* out) { std::memcpy(out, watched.data(), watched.size()); }
 int stub_graph_launches() { return graph_launches; }
 int stub_iterations() { return iterations; }
 int stub_syncs() { return syncs; }
@@ -83,6 +92,7 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
     const std::string& name = kernels[f];
     auto is = [&](const char* k) { return name.find(k) != std::string::npos; };
     auto ptr = [&](int i) { return *static_cast<void**>(args[i]); };
+    if (!watch.empty() && is(watch.c_str())) std::memcpy(watched.data(), args[watch_arg], watched.size());
     if (capture && !fail.empty() && is(fail.c_str())) return last = hipErrorLaunchFailure;
     Step s{name, is("k_pcg_reduce_beta") ? static_cast<State*>(ptr(3)) : nullptr};
     if (capture) {

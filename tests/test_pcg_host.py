@@ -117,3 +117,35 @@ stub.stub_set(9, 0, b"")
 out.append([cg.solve(b, x, stream=Stream())["iterations"], stub.stub_live_graphs()])
 """ % kernel)
     assert out == [[-7, 0, 0], [-7, 0, 0], [9, 1]]
+
+
+@pytest.mark.parametrize("n", [2, 3, 4])
+def test_smoother_weight_stays_in_fp64(stub, n):
+    """n <= 4: the table that the smoother's block inverse gets is D^{-1} itself
+    (1 / (lam_i s_x + lam_j s_y + lam_k s_z) in the inner precision, here FP32);
+    the Chebyshev weight is an FP64 argument of its own."""
+    out = stub("""
+N = %d
+plan, b, x, cg = mesh(N, 8)
+mg = tpfdm.MG(plan)
+cg.set_multigrid(mg)
+stub.stub_set(1, 0, b"")
+E = (ctypes.c_float * (N ** 2 + N ** 3))()
+w = ctypes.c_double()
+for arg, dst in ((3, E), (4, w)):
+    stub.stub_watch(b"k_mg_jacobi0", arg, ctypes.sizeof(dst))
+    cg.solve(b, x, inner=tpfdm.F32, stream=Stream())
+    stub.stub_watched(ctypes.byref(dst))
+    cg.set_multigrid(mg)
+S, lam = tpfdm.reference_eigen(N, 2.0, tpfdm.OP_CELL)
+out = [list(E), w.value, S.reshape(-1).tolist(), lam.tolist()]
+""" % n)
+    import math
+
+    import numpy as np
+    E, w, S, lam = out
+    lam = np.array(lam) / 8.0   # s_d = h on cubes of edge length 1/8
+    d = 1.0 / (lam[:, None, None] + lam[None, :, None] + lam[None, None, :])
+    assert np.allclose(E[:n * n], S, rtol=1.2e-7, atol=1e-7)
+    assert np.allclose(E[n * n:], d.reshape(-1), rtol=1.2e-7, atol=0.0)
+    assert abs(w - 1.0 / (1.1 - 0.9 * math.cos(math.pi / 6.0))) < 1e-14
