@@ -18,7 +18,7 @@
 // loads run while one computes, and a tile's operands are requested before its
 // factors are staged.  20011 blocks of n = 4, FP64, product and inverse
 // together: 27.7 us with 16 workgroups a CU looping over the tiles and the
-// factors of a tile unpadded, 21.3 us so; 43.6 -> 21.2 us for a drawn n = 3.
+// factors of a tile unpadded, 21.3 us so.
 //
 // Device layouts (plan-owned):
 //   fac[b][d][0 = M, 1 = P][n][n]          row-major
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(64, 2) void k_apply_gen(const TS* __restrict__ u, T
 }
 
 // Waves per SIMD of the inverse: 4 (n = 7 in FP64 else takes 138 registers and
-// runs 3: 59.5 -> 54.8 us for 20000 blocks), at n = 8 in FP64 3, which it
+// runs 3: 59.5 -> 54.8 us for 20000 blocks, one value spilled), at n = 8 in FP64 3, which it
 // reaches when the phases' lane test is not folded away (75.0 -> 65.4 us).
 template <int N, typename TC>
 constexpr int inverse_waves() {

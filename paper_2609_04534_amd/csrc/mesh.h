@@ -59,8 +59,8 @@ __device__ __forceinline__ unsigned lane_tile(unsigned b, unsigned nwg, unsigned
 }
 
 // The one-cell-per-wave kernels (n >= 5) sweep groups of 192 cells (n = 8 in
-// FP64 on 48^3 cells: 397 us in plain order, 374, 367, 368 and 373 us with 48,
-// 192, 384 and 768; FP32 and smaller n within 2%).
+// FP64 on 48^3 cells: 317 us in plain order, 306, 296, 299 and 302 us with 48,
+// 192, 384 and 768; FP32 within 4%, n = 6 within 1%).
 // WV > 1 (workgroups of WV waves, one cell each): groups of as many cells.
 template <int WV = 1>
 __device__ __forceinline__ unsigned wave_tile(unsigned b, unsigned nwg, const MeshArgs& G) {
@@ -70,10 +70,11 @@ __device__ __forceinline__ unsigned wave_tile(unsigned b, unsigned nwg, const Me
 // Row length S for lane_tile: the whole tiles of 64 W cells in an x-plane of
 // cells when one plane of blocks (n^3 values of T per cell) holds 2 MiB or
 // more, else 0 (plain order).  Coupled operator at n = 4, plain against
-// grouped order: FP64 128^3 cells (8 MiB planes) 663 / 568 us, 100^3 354 /
-// 315 us, 64^3 (2 MiB) 79 / 72 us; FP32 128^3 358 / 346 us; Hermite-type
-// basis 128^3 500 / 479 us.  Groups of 4 to 32 tiles differ by under 5%; at
-// n = 2 with 1 MiB planes the grouped order took 50 us against 46.
+// grouped order: FP64 128^3 cells (8 MiB planes) 655 / 550 us, 100^3 346 /
+// 300 us, 64^3 (2 MiB) 76 / 72 us; FP32 128^3 330 / 321 us; Hermite-type
+// basis 128^3 478 / 453 us.  With an earlier form of the row groups of 4 to 32
+// tiles differed by under 5%, and at n = 2 with 1 MiB planes the grouped order
+// took 50 us against 46.
 template <int N, typename T, int W>
 __device__ __forceinline__ unsigned plane_tiles(const MeshArgs& G) {
     constexpr int64_t kMinPlaneBytes = int64_t(2) << 20;

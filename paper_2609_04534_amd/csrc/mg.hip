@@ -13,18 +13,19 @@
 // inverse.  All tables (operator, inverse, transfers) are the plan's, in the
 // plan's basis.  Each update is one kernel in the factorized form the paper
 // describes (Sec. 5.2): the operator row, the residual, the block inverse
-// and the update of the lane's cell in registers, so no residual vector is
-// written; the first update from u = 0 needs no operator.  Updates alternate
+// and the update of a workgroup's cells in registers and LDS, so no residual
+// vector is written; the first update from u = 0 needs no operator.  Updates alternate
 // between the correction and one scratch vector per level.  Transfers embed
 // a coarse cell's polynomial into its eight children (prolongation, added
 // to the fine correction) and apply the transpose (restriction).  The coarsest level is solved exactly by a
 // dense inverse, assembled once by applying the level operator to unit
 // vectors (as the paper assembles its coarse LU) and inverted on the host.
 //
-// For n <= 4 every vector of a level is in the B = 64 blocked layout, one
-// cell per lane; for n >= 5 in the B = 1 layout, one cell per wave.  Every
-// kernel returns at once when the solve state passed to it is done,
-// so a V-cycle can sit inside a captured chunk of CG iterations.
+// For n <= 4 every vector of a level is in the B = 64 blocked layout, 64 or 128
+// cells per workgroup of n waves (a wave holds a plane of each cell); for n >= 5
+// in the B = 1 layout, one cell per wave.  Every kernel returns at once when the
+// solve state passed to it is done, so a V-cycle can sit inside captured CG
+// iterations.
 #include <algorithm>
 #include <cmath>
 #include <map>
@@ -55,8 +56,8 @@ __device__ __forceinline__ bool done_flag(const PcgState* st) { return st && st-
 // computed in MgTC<TS>: FP64 for FP64 storage, FP32 for FP32 storage (there
 // the level vectors carry FP32 rounding already, and the FP32 rows take half
 // the registers and LDS of FP64 ones); the smoother's block inverse runs in
-// TI, the transfers and the first update in FP64, and every kernel rounds
-// only where it stores.
+// TI, the updates u + omega D^{-1} r and the transfers in FP64, and every kernel
+// rounds only where it stores.
 template <typename TS>
 using MgTC = typename std::conditional<std::is_same<TS, float>::value, float, double>::type;
 

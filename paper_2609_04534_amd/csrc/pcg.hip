@@ -6,16 +6,20 @@
 // block inverse inside Chebyshev smoothing on every level; mg.hip), set with
 // tp_pcg_set_multigrid.
 //
-// One iteration is five launches, none of which needs the host:
+// One iteration is five launches (and a V-cycle's), none of which needs the host:
 //   1. q = A p with the per-workgroup partial sums of (p, q)
 //   2. one workgroup: alpha = (r, z) / (p, q)
 //   3. x += alpha p, r -= alpha q, z = D^{-1} r, partial sums of (r, z), (r, r)
+//      (with a V-cycle x, r and (r, r) here, then the cycle, whose last update
+//      leaves the sums of (r, z))
 //   4. one workgroup: beta = (r, z)_new / (r, z), convergence test on (r, r)
 //   5. p = z + beta p
 // The state (scalars, iteration count, done flag) lives in device memory;
 // once the flag is set every later kernel returns at its first instruction,
-// so the host enqueues iterations in chunks and reads the state once per
-// chunk.  Reductions sum per-workgroup partials in a fixed order (no
+// so the host enqueues iterations in captured graphs (check_every of them, with
+// a V-cycle at most four) and reads the state after each; a step of a
+// non-blocking solve is check_every iterations.  Reductions sum per-workgroup
+// partials in a fixed order (no
 // atomics), so a solve is deterministic.
 #include <algorithm>
 #include <cmath>

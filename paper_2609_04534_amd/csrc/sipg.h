@@ -136,7 +136,7 @@ __device__ __forceinline__ void wave_sipg_cell(const T* __restrict__ u, const Me
     const int pa = pc.pa, pb = pc.pb, lane = threadIdx.x;
     // FP64 at n = 8: every lane is active, but the compiler must not know, so
     // that the phases stay separate blocks; merged, the scalar tables of all of
-    // them are loaded ahead and spilled (48^3 cells: 362 us against 329)
+    // them are loaded ahead and spilled (48^3 cells: 310 us against 296)
     bool act = pc.act;
     if constexpr (Pencil<N>::kFull && sizeof(T) == 8) {
         int l = lane;

@@ -450,7 +450,8 @@ __device__ __forceinline__ void tile_sipg(const TS* __restrict__ u, const MeshAr
 
 // Waves per SIMD the tile kernels are built for.  n = 4 in FP64 with one
 // cell a lane needs 140 registers (four waves spill: 72 against 94 us on 64^3
-// cells); two cells a lane need up to 254.
+// cells); two cells a lane take up to all 256 of two waves (the Lagrange
+// kernels of n = 4 spill four to seven values).
 template <int N, typename TC, int W>
 constexpr int tile_waves() {
     return W == 2 ? 2 : (N == 4 && sizeof(TC) == 8 ? 3 : 4);
@@ -551,10 +552,11 @@ TileTab<N, TC, HERM> tile_tab(const Plan& plan, bool face_only) {
 // Whether a lane takes two cells (16-byte loads): FP64, pairs that stay
 // together (B = 64, an even cell count in z, 16-byte aligned vectors), and
 // enough cells that workgroups of 128 still cover the CUs.  Operator in FP64,
-// one against two cells a lane: 128^3 cells n = 2 76 / 60 us, n = 3 326 / 298
-// us, n = 4 740 / 600 us; 32^3 cells n = 4 14.0 / 12.1 us, n = 3 8.5 / 8.2 us,
-// n = 2 8.2 / 8.2 us; 8^3 cells n = 4 9.1 / 12.0 us.  FP32 loads (4 bytes a
-// lane) already run at the full rate and keep one cell.
+// one against two cells a lane: 128^3 cells n = 2 76 / 48 us, n = 3 293 / 244
+// us, n = 4 713 / 550 us; 100^3 n = 4 338 / 300 us; 64^3 n = 2 9.8 / 8.6 us, n =
+// 4 68 / 72 us; 32^3 n = 3 8.4 / 8.7 us, n = 4 10.9 / 11.4 us; with an earlier
+// form of the row 8^3 cells n = 4 9.1 / 12.0 us.  FP32 loads (4 bytes a lane)
+// already run at the full rate and keep one cell.
 inline bool tile_pairs(const MeshArgs& G, size_t elem, bool aligned) {
     constexpr int64_t kMinCells = 32768;
     return elem == 8 && aligned && G.logB == 6 && G.offset % 2 == 0 && G.mz % 2 == 0 && G.ncells >= kMinCells;
